@@ -1,7 +1,7 @@
 // Device-side state transfer between a bin's packed layout (q, v: 32 floats
 // per packed variant; k, status, counters per packed variant) and the
 // caller's variant-CSR layout in device memory (sim_get_state /
-// sim_set_state / sim_counters with where = SIM_DEVICE).
+// sim_set_state / sim_fitness / sim_counters with where = SIM_DEVICE).
 //
 // map[s] of packed variant s: (user index, offset of its q entries, offset of
 // its v entries, nq | nv << 16), built by sim_create and uploaded by sim_bind.
@@ -65,6 +65,17 @@ __global__ __launch_bounds__(256) void counters_gather_kernel(int m, const int4*
   if (status) status[u] = st[s];
 }
 
+// Fitness of a bin's packed variants into user order.  One launch per bin:
+// neighbours in a bin are rarely neighbours in user order (bins are sorted by
+// DoF count and depth), and a device copy per run of consecutive users cost
+// 4096 random trees more than the rollout itself (see sim_fitness).
+__global__ __launch_bounds__(256) void fitness_gather_kernel(int m, const int4* __restrict__ map,
+                                                             const float* __restrict__ fit, float* out) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= m) return;
+  out[map[s].x] = fit[s];
+}
+
 unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
 
 }  // namespace
@@ -82,6 +93,13 @@ hipError_t launch_state_scatter(int m, const int* map, const float* q, const flo
   if (m <= 0) return hipSuccess;
   hipLaunchKernelGGL(state_scatter_kernel, dim3(blocks_for((int64_t)m * kEntries)), dim3(256), 0, st, m,
                      reinterpret_cast<const int4*>(map), q, v, k, qb, vb, kb, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_fitness_gather(int m, const int* map, const float* fit, float* out, hipStream_t st) {
+  if (m <= 0) return hipSuccess;
+  hipLaunchKernelGGL(fitness_gather_kernel, dim3(blocks_for(m)), dim3(256), 0, st, m,
+                     reinterpret_cast<const int4*>(map), fit, out);
   return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@ hipError_t launch_state_gather(int m, const int* map, const float* qb, const flo
                                float* v, int64_t* k, hipStream_t st);
 hipError_t launch_state_scatter(int m, const int* map, const float* q, const float* v, const int64_t* k, float* qb,
                                 float* vb, long long* kb, unsigned* status, hipStream_t st);
+hipError_t launch_fitness_gather(int m, const int* map, const float* fit, float* out, hipStream_t st);
 hipError_t launch_counters_gather(int m, const int* map, const unsigned long long* cnt, const unsigned* status_b,
                                   uint64_t* rows_contact, uint64_t* rows_clamp, uint32_t* status, hipStream_t st);
 

@@ -763,17 +763,10 @@ int sim_fitness(const sim_handle* hc, float* out, int where, void* stream) {
     return SIM_OK;
   }
   if (where == SIM_DEVICE) {
-    // user-order scatter: one contiguous run per maximal block of consecutive user indices
     for (Bin& b : h->bins) {
-      size_t s = 0;
-      while (s < b.users.size()) {
-        size_t e = s + 1;
-        while (e < b.users.size() && b.users[e] == b.users[e - 1] + 1) ++e;
-        int rc = dev_check(h, hipMemcpyAsync(out + b.users[s], h->ws + b.o_fit + s * 4, (e - s) * 4,
-                                             hipMemcpyDeviceToDevice, st), "fitness scatter");
-        if (rc) return rc;
-        s = e;
-      }
+      int rc = dev_check(h, launch_fitness_gather((int)b.users.size(), (const int*)(h->ws + b.o_map), b.args.fit, out,
+                                                  st), "fitness gather");
+      if (rc) return rc;
     }
     return SIM_OK;
   }
