@@ -8,7 +8,7 @@
 
 namespace simk {
 
-#define SIMK_MULTI_FAMILIES(X) X(16, 2, 16) X(20, 2, 8) X(24, 2, 8) X(28, 2, 8)
+#define SIMK_MULTI_FAMILIES(X) X(16, 2, 8) X(16, 2, 16) X(20, 2, 8) X(24, 2, 8) X(28, 2, 8)
 
 #define SIMK_MULTI_ENTRY(NVC, SB, NCR) {NVC, SB, NCR},
 const MultiFamily kMultiFamilies[] = {SIMK_MULTI_FAMILIES(SIMK_MULTI_ENTRY)};
@@ -22,7 +22,7 @@ constexpr size_t max_size(size_t i = 0) {
 }
 constexpr size_t kMultiLdsBytes = max_size() * kVarPerWave;
 
-__global__ __launch_bounds__(64) void rollout_multi_kernel(MultiArgs m, ModelParams P) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void rollout_multi_kernel(MultiArgs m, ModelParams P) {
   __shared__ __attribute__((aligned(16))) char smem[kMultiLdsBytes];
   const int blk = blockIdx.x;
   int bi = 0;

@@ -243,36 +243,53 @@ __device__ __forceinline__ sv imul(const sinertia& J, const sv& V) {
 // ----------------------------------------------------------------------------
 // Per-variant LDS area.
 // ----------------------------------------------------------------------------
+// Parts whose lives do not meet share their words, so that two waves per SIMD
+// (eight per CU, at most 20 KB each) fit with the largest robots as well:
+//   A   forward pass: pose, velocity and bias acceleration of every body
+//       (24 words), its tail the joints' sines, cosines and rates, then the
+//       self-collision candidates; backward pass: composite inertia, force and
+//       C S in the same records, the tail the bias vector; then the assembled
+//       matrix; during the inverse the pivot column's broadcast buffers; after
+//       it the negated inverse;
+//   WO  forward and backward pass, contact geometry: hinge motion; from the
+//       contact rows on: the contacts' solver scalars.
+// A family of NVC DoFs has at most NVC + 1 bodies (a fixed root's).
+constexpr int cmax(int a, int b) { return a > b ? a : b; }
 template <int NVC, int SB, int NCR, bool BALL = false, bool SELF = false, bool TREE = false>
 struct alignas(16) GroupLds {
   static constexpr int NBC = 16 * SB;
+  static constexpr int NBL = NBC < NVC + 1 ? NBC : NVC + 1;  // bodies held
   static constexpr int MST = NVC + 1;                 // padded row stride of the matrices
-  static constexpr int A_BODY = NBC * 24;             // forward: R9 p3 V6 A6; backward: C10 F6
+  static constexpr int A_BODY = NBL * 24;             // forward: R9 p3 V6 A6; backward: C10 F6 (C S)6
   static constexpr int A_MAT = NVC * MST;             // assembled M~, later M~^-1 (rotated columns)
-  static constexpr int A_WORDS = A_BODY > A_MAT ? A_BODY : A_MAT;
+  static constexpr int MAXPAIRS = (NBL - 1) * (NBL - 2) / 2;  // body pairs not joined by a hinge
+  static constexpr int A_TAIL = cmax(3 * NVC, SELF ? (MAXPAIRS + 1) / 2 : 0);
+  static constexpr int A_WORDS = (cmax(A_BODY + A_TAIL, cmax(A_MAT, 2 * (2 * NVC + 16))) + 3) / 4 * 4;
+  static constexpr int WO_WORDS = (cmax(NBL * 6, NCR * 12) + 3) / 4 * 4;
   static_assert(A_MAT % 4 == 0, "the matrix area is cleared with 16-byte stores");
   float A[A_WORDS];
-  float WO[NBC][12];        // hinge axis w, linear part (o - p0) x w of its motion S, composite force C S
-  int par[NBC];
-  int ccount[NBC];          // active-corner mask per body
+  float WO[WO_WORDS];       // [body][6]: hinge axis w, linear part (o - p0) x w of its motion S; later
+                            // [contact][12]: solver scalars
   float cl[NCR][(BALL || SELF) ? kListWordsBall : kListWords];  // contact list entries (ListWord)
-  float cs[NCR][12];        // per-contact solver scalars
-  float sth[NVC], cth[NVC], thd[NVC];  // sin theta, cos theta, thetadot by DoF
-  float cvec[NVC];          // bias c by DoF
-  float cb[2][2 * NVC + 16];  // doubled broadcast buffers of the pivot column (+ a sink
-                              // for the lanes past the last DoF, which store unmasked)
-  int lv[2 * NBC + 4];      // level lists (bodies in depth order, then level starts), staged per launch
-  float brad[SELF ? NBC : 1];  // bounding-sphere radius |h| per body (self-collision), staged per launch
-  // self-collision: body pairs not joined by a hinge, in order (a | b << 8),
-  // built per launch; the step's bounding-sphere candidates among them
-  uint16_t spair[SELF ? NBC * (NBC - 1) / 2 : 1];
-  uint16_t scand[SELF ? NBC * (NBC - 1) / 2 : 1];
+  uint16_t lv[NBC];         // bodies in depth order (body | parent << 8), staged per launch
+  uint8_t ls[NBC + 4];      // where each depth level starts in lv
   // tree-sparse factorisation: the negated inverse (rows of M~^-1 in natural
   // column order), each DoF's path mask (itself and its ancestors) and the
   // reciprocal diagonal of the factor
   float X[TREE ? NVC * MST : 1];
   unsigned pm[TREE ? NVC : 1];
   float dinv[TREE ? NVC : 1];
+  __device__ __forceinline__ float* wo(int b) { return &WO[b * 6]; }
+  __device__ __forceinline__ float* scal(int c) { return &WO[c * 12]; }
+  __device__ __forceinline__ float* sth() { return &A[A_BODY]; }            // sin theta by DoF
+  __device__ __forceinline__ float* cth() { return &A[A_BODY + NVC]; }      // cos theta
+  __device__ __forceinline__ float* thd() { return &A[A_BODY + 2 * NVC]; }  // thetadot
+  __device__ __forceinline__ float* cvec() { return &A[A_BODY]; }           // bias c by DoF
+  // self-collision candidates of the step: body pairs a | b << 8
+  __device__ __forceinline__ uint16_t* cand() { return reinterpret_cast<uint16_t*>(&A[A_BODY]); }
+  // doubled broadcast buffers of the pivot column (+ a sink for the lanes past
+  // the last DoF, which store unmasked)
+  __device__ __forceinline__ float* cb(int i) { return &A[i * (2 * NVC + 16)]; }
 };
 
 // ----------------------------------------------------------------------------
@@ -283,10 +300,11 @@ struct alignas(16) GroupLds {
 // Builds J (normal z, tangents x, y) of the point x for the lane's DoF slots,
 // W = M~^-1 J^T, the row denominators and cross terms, and the solver scalars.
 // ----------------------------------------------------------------------------
-// Column C of three mat-vecs: y_k[s] += Mi[s][C] * x_k(DoF C), with x_k(DoF C)
-// read from lane C mod 16 of the row by the multiply-add itself
-// (v_fmac_f32 with a row_newbcast DPP source), so the broadcast costs no
-// separate move.  Same single rounding as fmaf(Mi, x, y).  The leading s_nop
+// Column C of three mat-vecs with the held (negated) inverse: y_k[s] -=
+// Mi[s][C] * x_k(DoF C), with x_k(DoF C) read from lane C mod 16 of the row and
+// its sign turned by the multiply-add itself (v_fmac_f32 with a negated
+// row_newbcast DPP source), so neither costs a separate instruction or
+// register.  Same single rounding as fmaf(Mi, -x, y).  The leading s_nop
 // gives the two wait states a DPP source needs after a VALU write, which the
 // compiler does not track across inline assembly.  Every lane of an active row
 // takes part (row-uniform control flow), as DPP reads require.
@@ -294,9 +312,9 @@ template <int L>
 __device__ __forceinline__ void fmac3_bcast(const float (&m)[1], float xa, float xb, float xc, float (&ya)[1],
                                             float (&yb)[1], float (&yc)[1]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, %3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %2, %5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0]), "+v"(yb[0]), "+v"(yc[0])
       : "v"(xa), "v"(xb), "v"(xc), "v"(m[0]), "n"(L));
 }
@@ -304,12 +322,12 @@ template <int L>
 __device__ __forceinline__ void fmac3_bcast(const float (&m)[2], float xa, float xb, float xc, float (&ya)[2],
                                             float (&yb)[2], float (&yc)[2]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, %6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, %6, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %2, %7, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %3, %7, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %4, %8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %5, %8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%6, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%7, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, -%7, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, -%8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, -%8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0]), "+v"(ya[1]), "+v"(yb[0]), "+v"(yb[1]), "+v"(yc[0]), "+v"(yc[1])
       : "v"(xa), "v"(xb), "v"(xc), "v"(m[0]), "v"(m[1]), "n"(L));
 }
@@ -327,12 +345,29 @@ __device__ __forceinline__ void matvec_bcast3(const float (&Mi)[S][NVC], const f
   }
 }
 
+// The same for one mat-vec, y[s] -= Mi[s][C] * x(DoF C).
+template <int L>
+__device__ __forceinline__ void fmac1_bcast(const float (&m)[1], float xa, float (&ya)[1]) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "+v"(ya[0])
+      : "v"(xa), "v"(m[0]), "n"(L));
+}
+template <int L>
+__device__ __forceinline__ void fmac1_bcast(const float (&m)[2], float xa, float (&ya)[2]) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, -%2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+v"(ya[0]), "+v"(ya[1])
+      : "v"(xa), "v"(m[0]), "v"(m[1]), "n"(L));
+}
 template <int S, int NVC, int C = 0>
 __device__ __forceinline__ void matvec_bcast1(const float (&Mi)[S][NVC], const float (&a)[S], float (&ya)[S]) {
   if constexpr (C < NVC) {
-    const float va = row_bcast<C % 16>(a[C / 16]);
+    float m[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) ya[s] = fmaf(Mi[s][C], va, ya[s]);
+    for (int s = 0; s < S; ++s) m[s] = Mi[s][C];
+    fmac1_bcast<C % 16>(m, a[C / 16], ya);
     matvec_bcast1<S, NVC, C + 1>(Mi, a, ya);
   }
 }
@@ -373,7 +408,6 @@ __device__ __forceinline__ void build_rows(const float (&Mi)[S][NVC], const f3 (
                                            const int (&bodyOfDof)[S], int lane, f3 x, unsigned anc, float kc,
                                            float kb, float dt, float (&Jn)[S], float (&Jx)[S], float (&Jy)[S],
                                            float (&Wn)[S], float (&Wx)[S], float (&Wy)[S], float (&scal)[10]) {
-  float nJn[S], nJx[S], nJy[S];  // sign of the held inverse folded in
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const bool on = (bodyOfDof[s] < 0) || ((anc >> bodyOfDof[s]) & 1u);
@@ -381,10 +415,9 @@ __device__ __forceinline__ void build_rows(const float (&Mi)[S][NVC], const f3 (
     Jn[s] = on ? J.z : 0.f;
     Jx[s] = on ? J.x : 0.f;
     Jy[s] = on ? J.y : 0.f;
-    nJn[s] = -Jn[s]; nJx[s] = -Jx[s]; nJy[s] = -Jy[s];
     Wn[s] = 0.f; Wx[s] = 0.f; Wy[s] = 0.f;
   }
-  matvec_bcast3<S, NVC>(Mi, nJn, nJx, nJy, Wn, Wx, Wy);
+  matvec_bcast3<S, NVC>(Mi, Jn, Jx, Jy, Wn, Wx, Wy);
   float pn = 0.f, px = 0.f, py = 0.f, pxn = 0.f, pyn = 0.f;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
@@ -423,7 +456,6 @@ __device__ __forceinline__ void build_rows_gen(const float (&Mi)[S][NVC], const 
                                                float (&Wx)[S], float (&Wy)[S], float (&scal)[10]) {
   f3 t1, t2;
   tangents(n, t1, t2);
-  float nJn[S], nJx[S], nJy[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int bd = bodyOfDof[s];
@@ -438,10 +470,9 @@ __device__ __forceinline__ void build_rows_gen(const float (&Mi)[S][NVC], const 
     Jn[s] = dot3(n, J);
     Jx[s] = dot3(t1, J);
     Jy[s] = dot3(t2, J);
-    nJn[s] = -Jn[s]; nJx[s] = -Jx[s]; nJy[s] = -Jy[s];
     Wn[s] = 0.f; Wx[s] = 0.f; Wy[s] = 0.f;
   }
-  matvec_bcast3<S, NVC>(Mi, nJn, nJx, nJy, Wn, Wx, Wy);
+  matvec_bcast3<S, NVC>(Mi, Jn, Jx, Jy, Wn, Wx, Wy);
   float pn = 0.f, px = 0.f, py = 0.f, pxn = 0.f, pyn = 0.f;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
@@ -771,22 +802,26 @@ __device__ __forceinline__ int row_min_i(int x) {
 // ----------------------------------------------------------------------------
 // The kernel.
 // ----------------------------------------------------------------------------
-// A budget of 256 registers (two waves per SIMD) for the families that fit it
-// without spills: one DoF slot per lane with at most 2 contacts in registers,
-// and the 16-DoF families with 8; and for the 20-DoF, 16-body families with 2
-// or 4 contacts in registers, which spill 24 and 48 registers per lane at
-// 256 but run faster at two waves per SIMD: with 2, the whole rollout of the
-// 8192 random trees is 5 % faster than with the single-wave 32-body kernel,
-// with 4 another 3 % (more contacts stay out of the workspace; 5 is no
-// faster, 6 slower).  The 24- and 28-DoF families spill 196 and 272 bytes
-// there and run slower.  Their LDS areas then admit two waves per SIMD with
-// 16 body slots and 1.5 with 32.  The others may use the whole register file
-// and run one wave per SIMD.
-template <int NVC, int SB, int NCR>
+// Waves per SIMD, i.e. the register budget (512, 256, 168 or 128 a wave).  A
+// wave alone on a SIMD issues one instruction of any kind in four cycles,
+// while two together issue an FMA, add, multiply or move in about two each
+// (DPP, compares, selects and scalar operands in four): measured on gfx950.
+// So every family gets the most waves its live values allow without scratch:
+// 28 DoFs with 8 contacts in registers hold 56 words of the inverse and 96 of
+// contact rows beside about 70 of state.  What made room: addresses and lane
+// conditions are formed again in each step (hoisted they held 100 registers),
+// overflow contacts are built before the register ones, the free velocity is
+// not sunk below the contact rows.  With the LDS areas at most 1/8 of a CU's
+// 160 KB, 8192 quadrupeds x 500 steps take 25.6 ms (39.3 with one wave per
+// SIMD), 32768 boxes with a ball x 1000 steps 48.9 ms with three waves (66.1
+// with two, 113 with one).  12 contacts in registers, balls on the largest
+// robots and the tree-sparse inverse do not fit 256 and keep one wave.
+template <int NVC, int SB, int NCR, bool BALL, bool SELF, bool TREE>
 struct WavesPerSimd {
-  static constexpr int value =
-      ((SB == 1 && NCR <= 2 && NVC <= 20) || (SB == 1 && NCR == 4 && NVC == 20) || (NCR == 8 && NVC == 16)) ? 2
-                                                                                                             : 1;
+  static constexpr int value = TREE || NCR > 8 && NVC > 16 || BALL && NVC > 24 ? 1
+                               : NVC > 16 || NCR > 8                          ? 2
+                               : BALL || SELF || NVC <= 12                    ? 3
+                                                                              : 4;
 };
 
 // One workgroup (one wave, four variants) of a bin: `block` is the
@@ -803,9 +838,9 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
   static_assert(!TREE || (NVC >= 8 && NVC <= 32), "path masks are 32-bit; the first six DoFs are held apart");
   constexpr int MST = L::MST;
 
-  const int lane = threadIdx.x & 15;
+  int lane = threadIdx.x & 15;
   const int grp = threadIdx.x >> 4;
-  const int vid = block * kVarPerWave + grp;
+  int vid = block * kVarPerWave + grp;
   if (vid >= a.n) return;  // whole rows leave together
   L& sh = lds_all[grp];
 
@@ -817,12 +852,28 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
   const float mu = hf[HF_MU];
   const float rball = BALL ? hf[HF_BALLR] : 0.f, mball = BALL ? hf[HF_BALLM] : 0.f;
   const float iball = 0.4f * mball * rball * rball;  // solid sphere
-  const float* bodyv = a.body + (size_t)vid * NBC * BW_WORDS;
+  // body records and overflow scratch: a wave-uniform base (scalar registers)
+  // plus a 32-bit byte offset of the lane's variant, so that no 64-bit lane
+  // pointer is held
+  const char* const bodyU = reinterpret_cast<const char*>(a.body + (size_t)block * kVarPerWave * NBC * BW_WORDS);
+  char* const ovfU = reinterpret_cast<char*>(a.ovf + (size_t)block * kVarPerWave * a.ovf_stride);
+  unsigned body_off = (unsigned)grp * (NBC * BW_WORDS * 4);
+  unsigned ovf_off = (unsigned)grp * ((unsigned)a.ovf_stride * 4u);
+  auto body_rec = [&](int b) {
+    return reinterpret_cast<const float*>(bodyU + (size_t)(body_off + (unsigned)b * (BW_WORDS * 4u)));
+  };
+  // overflow contact c: list entry, solver scalars, rows (ovf_floats layout)
+  auto ovf_entry = [&](int c) {
+    return reinterpret_cast<float*>(ovfU + (size_t)(ovf_off + (unsigned)c * (CLW * 4u)));
+  };
+  auto ovf_scalars = [&](int c) {
+    return reinterpret_cast<float*>(ovfU + (size_t)(ovf_off + MAXC * CLW * 4u + (unsigned)c * (kOvfScal * 4u)));
+  };
+  auto ovf_row = [&](int c) {
+    return reinterpret_cast<float*>(
+        ovfU + (size_t)(ovf_off + MAXC * (CLW + kOvfScal) * 4u + (unsigned)c * (6u * NVC * 4u)));
+  };
   const int* lvl = a.lvl + (size_t)vid * a.lvl_stride;  // bodies in level order, then level offsets
-  float* ovf = a.ovf + (size_t)vid * a.ovf_stride;
-  float* ovf_list = ovf;
-  float* ovf_scal = ovf + MAXC * CLW;
-  float* ovf_rows = ovf_scal + MAXC * kOvfScal;
 
   const float dt = P.dt, kp = P.kp, kd = P.kd, tmax = P.tau_max, kc = P.k_contact, bc = P.b_contact;
   const float ba = kd + dt * kp;
@@ -835,7 +886,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
   float pb[3] = {0.f, 0.f, 0.f}, Qb[4] = {1.f, 0.f, 0.f, 0.f};  // ball centre and orientation
   long long kstep;
   unsigned status;
-  unsigned long long cnt_contact, cnt_clamp;
+  unsigned n_contact = 0, n_clamp = 0;  // rows of this launch (at most kMaxStepsPerLaunch steps)
   {
     const float* qsrc = (a.reset ? a.q0 : a.q) + (size_t)vid * kQStride;
     const float* vsrc = (a.reset ? a.v0 : a.v) + (size_t)vid * kVStride;
@@ -859,27 +910,24 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       Q0[0] = hf[HF_ROOTQ]; Q0[1] = hf[HF_ROOTQ + 1]; Q0[2] = hf[HF_ROOTQ + 2]; Q0[3] = hf[HF_ROOTQ + 3];
     }
     if (a.reset) {
-      kstep = 0; status = 0; cnt_contact = 0; cnt_clamp = 0;
+      kstep = 0; status = 0;
     } else {
       kstep = a.k[vid]; status = a.status[vid];
-      cnt_contact = a.cnt[2 * vid]; cnt_clamp = a.cnt[2 * vid + 1];
     }
   }
   if (a.reset && lane == 0) {
     a.xy0[2 * vid] = (r0 == 6) ? p0[0] : 0.f;
     a.xy0[2 * vid + 1] = (r0 == 6) ? p0[1] : 0.f;
   }
-  unsigned ancS[SB];  // ancestors-or-self mask of the lane's body slots (CRBA)
 #pragma unroll
   for (int t = 0; t < SB; ++t) {
     const int b = lane + 16 * t;
-    ancS[t] = 0u;
     if (b < nb) {
-      sh.par[b] = __float_as_int(bodyv[b * BW_WORDS + BW_PARENT]);
-      ancS[t] = __float_as_uint(bodyv[b * BW_WORDS + BW_ANCESTORS]);
+      const int bl = lvl[b];  // the b-th body in depth order
+      sh.lv[b] = (uint16_t)(bl | ((__float_as_int(body_rec(bl)[BW_PARENT]) & 0xff) << 8));
     }
   }
-  for (int j = lane; j < 2 * NBC + 4; j += 16) sh.lv[j] = lvl[j];
+  for (int j = lane; j < NBC + 4; j += 16) sh.ls[j] = (uint8_t)lvl[NBC + j];
   if constexpr (TREE) {
     // path mask of every DoF (the DoF and its ancestors in the DoF tree): the
     // free root's six DoFs form a chain, a hinge sits under its parent body's
@@ -889,42 +937,52 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     for (int t = 0; t < SB; ++t) {
       const int b = lane + 16 * t;
       if (b >= 1 && b < nb && r0 + b - 1 < NVC)
-        sh.pm[r0 + b - 1] = (r0 == 6 ? 0x3Fu : 0u) | (((ancS[t] & ~1u) >> 1) << r0);
+        sh.pm[r0 + b - 1] = (r0 == 6 ? 0x3Fu : 0u) | (((__float_as_uint(body_rec(b)[BW_ANCESTORS]) & ~1u) >> 1) << r0);
     }
     for (int d = lane; d < NVC; d += 16) {
       if (r0 == 6 && d < 6) sh.pm[d] = (2u << d) - 1u;
       else if (d >= nvr) sh.pm[d] = 1u << d;
     }
   }
+  // self-collision: the pairs of bodies not joined by a hinge, in order, each
+  // with the squared reach of its two bounding spheres (radius |h|), built once
+  // per launch.  They lie in the rows of the scratch area's first NCR contacts,
+  // which never go there; read 16 at a time every step, they cost no LDS.
+  static_assert(!SELF || L::MAXPAIRS * 2 <= 6 * NVC * NCR, "the pair table fits in the unused rows");
+  auto pair_rec = [&](int k) { return ovf_row(0) + 2 * k; };
   int npairs = 0;  // row-uniform
   if (SELF) {
-#pragma unroll
-    for (int t = 0; t < SB; ++t) {
-      const int b = lane + 16 * t;
-      if (b < nb) {
-        const float* rec = bodyv + (size_t)b * BW_WORDS;
-        const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
-        sh.brad[b] = sqrtf(dot3(h, h));
-      }
-    }
-    wave_sync();  // parents staged above
-    // the pair table: for each a the lanes take b = a + 1 + lane (+16), a DPP
-    // scan places the pairs not joined by a hinge in order
+    // for each a the lanes take b = a + 1 + lane (+16), a DPP scan places the
+    // pairs not joined by a hinge in order
     for (int ia = 0; ia < nb - 1; ++ia) {
+      const float* ra = body_rec(ia);
+      const f3 ha = mk(ra[BW_HALF], ra[BW_HALF + 1], ra[BW_HALF + 2]);
 #pragma unroll
       for (int t = 0; t < SB; ++t) {
         const int ib = ia + 1 + lane + 16 * t;
-        const int ok = (ib < nb && sh.par[ib] != ia) ? 1 : 0;
+        const int ok = (ib < nb && __float_as_int(body_rec(ib)[BW_PARENT]) != ia) ? 1 : 0;
         const int incl = row_scan_incl(ok);
-        if (ok) sh.spair[npairs + incl - 1] = (uint16_t)(ia | (ib << 8));
+        if (ok) {
+          const float* rb = body_rec(ib);
+          const f3 hb = mk(rb[BW_HALF], rb[BW_HALF + 1], rb[BW_HALF + 2]);
+          const float ba2 = sqrtf(dot3(ha, ha)), bb2 = sqrtf(dot3(hb, hb));
+          const float rr = ba2 + bb2;
+          float* pe = pair_rec(npairs + incl - 1);
+          pe[0] = __int_as_float(ia | (ib << 8));
+          pe[1] = rr * rr * 1.0001f;
+        }
         npairs += row_bcast_i<15>(incl);
       }
     }
+    __threadfence_block();  // read by other lanes of the row
   }
   wave_sync();
 
   for (int it = 0; it < a.n_steps; ++it) {
     if (status) break;  // frozen variants stop (row-uniform)
+    // addresses are formed where they are used: hoisted out of the step loop
+    // they would hold some fifty registers through every phase
+    asm volatile("" : "+v"(lane), "+v"(body_off), "+v"(ovf_off));
 
     // =====================================================================
     // 1. forward kinematics, spatial velocities and bias accelerations, body
@@ -936,22 +994,20 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       const int d = lane + 16 * s;
       float sn, cn;
       sincos_moderate(thS[s], &sn, &cn);
-      if (d < NVC) { sh.sth[d] = sn; sh.cth[d] = cn; sh.thd[d] = vS[s]; }
+      if (d < NVC) { sh.sth()[d] = sn; sh.cth()[d] = cn; sh.thd()[d] = vS[s]; }
     }
     f3 wb = mk(row_bcast<0>(vS[0]), row_bcast<1>(vS[0]), row_bcast<2>(vS[0]));
     f3 vb = mk(row_bcast<3>(vS[0]), row_bcast<4>(vS[0]), row_bcast<5>(vS[0]));
     if (r0 != 6) { wb = mk(0.f, 0.f, 0.f); vb = wb; }
     const m33 R0 = quat_rot(Q0[0], Q0[1], Q0[2], Q0[3]);
     const f3 P0 = mk(p0[0], p0[1], p0[2]);
-#pragma unroll
-    for (int t = 0; t < SB; ++t) sh.ccount[lane + 16 * t] = 0;
     wave_sync();
 
     for (int lev = 0; lev <= maxdepth; ++lev) {
-      const int i1 = sh.lv[NBC + lev + 1];
-      for (int i = sh.lv[NBC + lev] + lane; i < i1; i += 16) {
-        const int b = sh.lv[i];
-        const float* rec = bodyv + (size_t)b * BW_WORDS;
+      const int i1 = sh.ls[lev + 1];
+      for (int i = sh.ls[lev] + lane; i < i1; i += 16) {
+        const int bl = sh.lv[i], b = bl & 0xff;
+        const float* rec = body_rec(b);
         m33 R;
         f3 p, w, o, sl = mk(0.f, 0.f, 0.f);
         sv V, A;
@@ -965,8 +1021,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           A.a = mk(0.f, 0.f, 0.f);
           A.l = mk(-P.g[0], -P.g[1], -P.g[2]);  // gravity as a base acceleration
         } else {
-          const int lam = sh.par[b];
-          const float* pr = &sh.A[lam * 24];
+          const float* pr = &sh.A[(bl >> 8) * 24];
           m33 Rl;
 #pragma unroll
           for (int k2 = 0; k2 < 9; ++k2) Rl.m[k2] = pr[k2];
@@ -974,7 +1029,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           const sv Vl = {mk(pr[12], pr[13], pr[14]), mk(pr[15], pr[16], pr[17])};
           const sv Al = {mk(pr[18], pr[19], pr[20]), mk(pr[21], pr[22], pr[23])};
           const int dof = r0 + b - 1;
-          const float sn = sh.sth[dof], cs = sh.cth[dof], thd = sh.thd[dof];
+          const float sn = sh.sth()[dof], cs = sh.cth()[dof], thd = sh.thd()[dof];
           const f3 u = mk(rec[BW_AXIS], rec[BW_AXIS + 1], rec[BW_AXIS + 2]);
           const m33 E = matmul(quat_rot(rec[BW_RQ], rec[BW_RQ + 1], rec[BW_RQ + 2], rec[BW_RQ + 3]),
                                axis_rot_acc(u, sn, cs));
@@ -994,33 +1049,38 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         dst[9] = p.x; dst[10] = p.y; dst[11] = p.z;
         dst[12] = V.a.x; dst[13] = V.a.y; dst[14] = V.a.z; dst[15] = V.l.x; dst[16] = V.l.y; dst[17] = V.l.z;
         dst[18] = A.a.x; dst[19] = A.a.y; dst[20] = A.a.z; dst[21] = A.l.x; dst[22] = A.l.y; dst[23] = A.l.z;
-        sh.WO[b][0] = w.x; sh.WO[b][1] = w.y; sh.WO[b][2] = w.z;
-        sh.WO[b][3] = sl.x; sh.WO[b][4] = sl.y; sh.WO[b][5] = sl.z;
-        // box-plane contact: 8 corners, bits (x, y, z) of the corner index = sign
-        if (b >= 1 || r0 == 6) {
-          const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
-          unsigned msk = 0u;
-#pragma unroll
-          for (int cn = 0; cn < 8; ++cn) {
-            const float z = p.z + R.m[6] * ((cn & 1) ? h.x : -h.x) + R.m[7] * ((cn & 2) ? h.y : -h.y) +
-                            R.m[8] * ((cn & 4) ? h.z : -h.z);
-            if (z < 0.f) msk |= 1u << cn;
-          }
-          sh.ccount[b] = (int)msk;
-        }
+        sh.wo(b)[0] = w.x; sh.wo(b)[1] = w.y; sh.wo(b)[2] = w.z;
+        sh.wo(b)[3] = sl.x; sh.wo(b)[4] = sl.y; sh.wo(b)[5] = sl.z;
       }
       wave_sync();
     }
     // contact list in (body, corner) order: prefix over bodies of the popcounts
     int nc = 0;
     {
-      // active corners per body, exclusive prefix over bodies by a DPP scan
+      // box-plane contact of every body at once (the lane's body slots, off the
+      // level chain): 8 corners, bits (x, y, z) of the corner index = sign; then
+      // an exclusive prefix over bodies of the active corners by a DPP scan
       // across the row (slot 0 holds bodies 0..15, slot 1 bodies 16..31)
       int off[SB];
+      unsigned mskS[SB];
 #pragma unroll
       for (int t = 0; t < SB; ++t) {
         const int b = lane + 16 * t;
-        const int cnt = (b < nb) ? __builtin_popcount((unsigned)sh.ccount[b]) : 0;
+        unsigned msk = 0u;
+        if (b < nb && (b >= 1 || r0 == 6)) {
+          const float* pr = &sh.A[b * 24];
+          const float* rec = body_rec(b);
+          const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
+          const float R6 = pr[6], R7 = pr[7], R8 = pr[8], pz = pr[11];
+#pragma unroll
+          for (int cn = 0; cn < 8; ++cn) {
+            const float z = pz + R6 * ((cn & 1) ? h.x : -h.x) + R7 * ((cn & 2) ? h.y : -h.y) +
+                            R8 * ((cn & 4) ? h.z : -h.z);
+            if (z < 0.f) msk |= 1u << cn;
+          }
+        }
+        mskS[t] = msk;
+        const int cnt = __builtin_popcount(msk);
         const int incl = row_scan_incl(cnt);
         off[t] = nc + incl - cnt;
         nc += row_bcast_i<15>(incl);
@@ -1029,10 +1089,10 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       for (int t = 0; t < SB; ++t) {
         const int b = lane + 16 * t;
         if (b < nb) {
-          const unsigned msk = (unsigned)sh.ccount[b];
+          const unsigned msk = mskS[t];
           if (msk) {
             const float* pr = &sh.A[b * 24];
-            const float* rec = bodyv + (size_t)b * BW_WORDS;
+            const float* rec = body_rec(b);
             const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
             const unsigned anc = __float_as_uint(rec[BW_ANCESTORS]);
             int idx = off[t];
@@ -1044,7 +1104,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
                                 pr[11] + pr[6] * sv3.x + pr[7] * sv3.y + pr[8] * sv3.z);
                 const f3 up = mk(0.f, 0.f, 1.f);
                 if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, anc, 0u, up, -x.z, 0);
-                else put_contact<GEN>(&ovf_list[idx * CLW], x, anc, 0u, up, -x.z, 0);
+                else put_contact<GEN>(ovf_entry(idx), x, anc, 0u, up, -x.z, 0);
                 ++idx;
               }
             }
@@ -1061,19 +1121,19 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       for (int k0 = 0; k0 < npairs; k0 += 16) {
         const int k = k0 + lane;
         int cand = 0;
-        uint16_t pr = 0;
+        int pr = 0;
         if (k < npairs) {
-          pr = sh.spair[k];
+          const float2 pe = *reinterpret_cast<const float2*>(pair_rec(k));
+          pr = __float_as_int(pe.x);
           const int ia = pr & 0xff, ib = pr >> 8;
           const float* pa = &sh.A[ia * 24];
           const float* pb = &sh.A[ib * 24];
           const f3 d = mk(pb[9] - pa[9], pb[10] - pa[10], pb[11] - pa[11]);
-          const float rr = sh.brad[ia] + sh.brad[ib];
-          cand = dot3(d, d) <= rr * rr * 1.0001f ? 1 : 0;
+          cand = dot3(d, d) <= pe.y ? 1 : 0;
         }
         if (__builtin_amdgcn_ballot_w64(cand != 0) == 0) continue;  // no candidate in any row of the wave
         const int incl = row_scan_incl(cand);
-        if (cand) sh.scand[ncand + incl - 1] = pr;
+        if (cand) sh.cand()[ncand + incl - 1] = (uint16_t)pr;
         ncand += row_bcast_i<15>(incl);
       }
       wave_sync();  // candidates written by other lanes of the row
@@ -1087,10 +1147,10 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         f3 ex = mk(0.f, 0.f, 0.f), en = ex;  // the edge-edge contact's point and normal (towards a)
         float ed = 0.f;
         int ia = 0, ib = 0;
-        m33 Ra, Rb;
+        m33 Ra = {}, Rb = {};  // (left undefined, they would stay live from step to step)
         f3 Pa = mk(0.f, 0.f, 0.f), Pb = Pa, ha = Pa, hb = Pa;
         if (ci < ncand) {
-          const uint16_t pr = sh.scand[ci];
+          const uint16_t pr = sh.cand()[ci];
           ia = pr & 0xff;
           ib = pr >> 8;
           const float* pa = &sh.A[ia * 24];
@@ -1101,8 +1161,8 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           for (int k2 = 0; k2 < 9; ++k2) Rb.m[k2] = pb[k2];
           Pa = mk(pa[9], pa[10], pa[11]);
           Pb = mk(pb[9], pb[10], pb[11]);
-          const float* reca = bodyv + (size_t)ia * BW_WORDS;
-          const float* recb = bodyv + (size_t)ib * BW_WORDS;
+          const float* reca = body_rec(ia);
+          const float* recb = body_rec(ib);
           ha = mk(reca[BW_HALF], reca[BW_HALF + 1], reca[BW_HALF + 2]);
           hb = mk(recb[BW_HALF], recb[BW_HALF + 1], recb[BW_HALF + 2]);
           for (int c = 0; c < 8; ++c)
@@ -1128,8 +1188,8 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         const int incl = row_scan_incl(cnt);
         if (hits | fmask) {
           int idx = nc + incl - cnt;
-          const unsigned anca = __float_as_uint(bodyv[(size_t)ia * BW_WORDS + BW_ANCESTORS]);
-          const unsigned ancb = __float_as_uint(bodyv[(size_t)ib * BW_WORDS + BW_ANCESTORS]);
+          const unsigned anca = __float_as_uint(body_rec(ia)[BW_ANCESTORS]);
+          const unsigned ancb = __float_as_uint(body_rec(ib)[BW_ANCESTORS]);
           if (fmask) {  // the clipped incident face again (same inputs, same points)
             FaceClip F;
             face_setup(Pa, Ra, ha, Pb, Rb, hb, face, F);
@@ -1141,13 +1201,13 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
               float dep;
               face_candidate(F, c, x, dep);
               if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, plus, minus, F.n, dep, 3);
-              else if (idx < MAXC) put_contact<GEN>(&ovf_list[idx * CLW], x, plus, minus, F.n, dep, 3);
+              else if (idx < MAXC) put_contact<GEN>(ovf_entry(idx), x, plus, minus, F.n, dep, 3);
               ++idx;
             }
           }
           if (hits == (1u << 16)) {
             if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], ex, anca, ancb, en, ed, 3);
-            else if (idx < MAXC) put_contact<GEN>(&ovf_list[idx * CLW], ex, anca, ancb, en, ed, 3);
+            else if (idx < MAXC) put_contact<GEN>(ovf_entry(idx), ex, anca, ancb, en, ed, 3);
             hits = 0u;
           }
           const f3 u = sat_axis(Pa, Ra, ha, Pb, Rb, hb);  // from b towards a
@@ -1160,7 +1220,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
                                       : dot3(n, Pa) + box_radius(Ra, ha, n) - dot3(n, x);
             const unsigned plus = aside ? anca : ancb, minus = aside ? ancb : anca;
             if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, plus, minus, n, depth, 3);
-            else if (idx < MAXC) put_contact<GEN>(&ovf_list[idx * CLW], x, plus, minus, n, depth, 3);
+            else if (idx < MAXC) put_contact<GEN>(ovf_entry(idx), x, plus, minus, n, depth, 3);
             ++idx;
           }
         }
@@ -1181,7 +1241,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         if (lane == 0) {
           const f3 x = mk(cb.x, cb.y, cb.z - rball);
           if (nc < NCR) put_contact<GEN>(&sh.cl[nc][0], x, 0u, 0u, mk(0.f, 0.f, 1.f), -x.z, 1);
-          else put_contact<GEN>(&ovf_list[nc * CLW], x, 0u, 0u, mk(0.f, 0.f, 1.f), -x.z, 1);
+          else put_contact<GEN>(ovf_entry(nc), x, 0u, 0u, mk(0.f, 0.f, 1.f), -x.z, 1);
         }
         ++nc;
       }
@@ -1196,7 +1256,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           m33 R;
 #pragma unroll
           for (int k2 = 0; k2 < 9; ++k2) R.m[k2] = pr[k2];
-          const float* rec = bodyv + (size_t)b * BW_WORDS;
+          const float* rec = body_rec(b);
           hit = sphere_box(cb, rball, mk(pr[9], pr[10], pr[11]), R,
                            mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]), x, n, depth);
         }
@@ -1204,13 +1264,14 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         const int incl = row_scan_incl(cnt);
         if (hit) {
           const int idx = nc + incl - cnt;
-          const unsigned anc = __float_as_uint(bodyv[(size_t)b * BW_WORDS + BW_ANCESTORS]);
+          const unsigned anc = __float_as_uint(body_rec(b)[BW_ANCESTORS]);
           if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, 0u, anc, n, depth, 2);
-          else put_contact<GEN>(&ovf_list[idx * CLW], x, 0u, anc, n, depth, 2);
+          else put_contact<GEN>(ovf_entry(idx), x, 0u, anc, n, depth, 2);
         }
         nc += row_bcast_i<15>(incl);
       }
     }
+    asm volatile("" : "+v"(nc));  // one register, not its addends
     __threadfence_block();  // overflow list entries are read by other lanes of the row
     wave_sync();
 
@@ -1225,7 +1286,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     for (int t = 0; t < SB; ++t) {
       const int b = lane + 16 * t;
       if (b < nb) {
-        const float* rec = bodyv + (size_t)b * BW_WORDS;
+        const float* rec = body_rec(b);
         float* own = &sh.A[b * 24];
         sinertia C;
         sv F;
@@ -1263,10 +1324,10 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     wave_sync();
     // then the subtrees level by level up the tree
     for (int lev = maxdepth; lev >= 0; --lev) {
-      const int i1 = sh.lv[NBC + lev + 1];
-      for (int i = sh.lv[NBC + lev] + lane; i < i1; i += 16) {
-        const int b = sh.lv[i];
-        const float* rec = bodyv + (size_t)b * BW_WORDS;
+      const int i1 = sh.ls[lev + 1];
+      for (int i = sh.ls[lev] + lane; i < i1; i += 16) {
+        const int b = sh.lv[i] & 0xff;
+        const float* rec = body_rec(b);
         float* own = &sh.A[b * 24];
         sinertia C;
         sv F;
@@ -1294,11 +1355,11 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         own[10] = F.a.x; own[11] = F.a.y; own[12] = F.a.z;
         own[13] = F.l.x; own[14] = F.l.y; own[15] = F.l.z;
         if (b >= 1) {
-          const sv Sb = {mk(sh.WO[b][0], sh.WO[b][1], sh.WO[b][2]), mk(sh.WO[b][3], sh.WO[b][4], sh.WO[b][5])};
-          sh.cvec[r0 + b - 1] = dot3(Sb.a, F.a) + dot3(Sb.l, F.l);
+          const sv Sb = {mk(sh.wo(b)[0], sh.wo(b)[1], sh.wo(b)[2]), mk(sh.wo(b)[3], sh.wo(b)[4], sh.wo(b)[5])};
+          sh.cvec()[r0 + b - 1] = dot3(Sb.a, F.a) + dot3(Sb.l, F.l);
           const sv Fc = imul(C, Sb);
-          sh.WO[b][6] = Fc.a.x; sh.WO[b][7] = Fc.a.y; sh.WO[b][8] = Fc.a.z;
-          sh.WO[b][9] = Fc.l.x; sh.WO[b][10] = Fc.l.y; sh.WO[b][11] = Fc.l.z;
+          own[16] = Fc.a.x; own[17] = Fc.a.y; own[18] = Fc.a.z;
+          own[19] = Fc.l.x; own[20] = Fc.l.y; own[21] = Fc.l.z;
         }
       }
       wave_sync();
@@ -1317,7 +1378,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       const f3 Fa = mk(src[10], src[11], src[12]), Fl = mk(src[13], src[14], src[15]);
       const f3 ca = mulT(R0, Fa), cl = mulT(R0, Fl);
       const int i = lane;
-      sh.cvec[i] = (i < 3) ? (i == 0 ? ca.x : i == 1 ? ca.y : ca.z) : (i == 3 ? cl.x : i == 4 ? cl.y : cl.z);
+      sh.cvec()[i] = (i < 3) ? (i == 0 ? ca.x : i == 1 ? ca.y : ca.z) : (i == 3 ? cl.x : i == 4 ? cl.y : cl.z);
       // M_rr = [[R^T Io R, [h_b]x], [[h_b]x^T, m 1]] with h_b = R^T h; column j of [h_b]x is h_b x e_j
       const f3 hb = mulT(R0, hw);
       const f3 hx0 = cross3(hb, mk(1.f, 0.f, 0.f)), hx1 = cross3(hb, mk(0.f, 1.f, 0.f)),
@@ -1337,8 +1398,22 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       }
     }
     if (BALL && lane < 6)  // ball: bias -m g on the centre velocity, none on the spin
-      sh.cvec[nvr + lane] = lane < 3 ? 0.f : -mball * (lane == 3 ? P.g[0] : lane == 4 ? P.g[1] : P.g[2]);
+      sh.cvec()[nvr + lane] = lane < 3 ? 0.f : -mball * (lane == 3 ? P.g[0] : lane == 4 ? P.g[1] : P.g[2]);
     wave_sync();  // composite reads done; the area becomes the assembled matrix
+    float cS[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int d = lane + 16 * s;
+      cS[s] = (d < nv) ? sh.cvec()[d] : 0.f;
+    }
+    float CS[SB][6];  // C S of the lane's bodies
+#pragma unroll
+    for (int t = 0; t < SB; ++t) {
+      const float* own = &sh.A[(lane + 16 * t < nb ? lane + 16 * t : 0) * 24];
+#pragma unroll
+      for (int k2 = 0; k2 < 6; ++k2) CS[t][k2] = own[16 + k2];
+    }
+    wave_sync();  // bias and C S lie in the area too
     {
       float4* a4 = reinterpret_cast<float4*>(sh.A);  // A is 16-byte aligned (first member)
       for (int e = lane; e < (NVC * MST + 3) / 4; e += 16) a4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1361,16 +1436,16 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         const int b = lane + 16 * t;
         if (b >= 1 && b < nb) {
           const int d = r0 + b - 1;
-          const sv Fcb = {mk(sh.WO[b][6], sh.WO[b][7], sh.WO[b][8]), mk(sh.WO[b][9], sh.WO[b][10], sh.WO[b][11])};
+          const sv Fcb = {mk(CS[t][0], CS[t][1], CS[t][2]), mk(CS[t][3], CS[t][4], CS[t][5])};
           // the hinges of b and its ancestors (the core has none), by the
           // ancestor mask: no pointer chase through LDS
-          unsigned am = ancS[t] & ~1u;
+          unsigned am = __float_as_uint(body_rec(b)[BW_ANCESTORS]) & ~1u;
           while (am) {
             const int j = __builtin_ctz(am);
             am &= am - 1u;
             const int dj = r0 + j - 1;
-            const f3 wj = mk(sh.WO[j][0], sh.WO[j][1], sh.WO[j][2]);
-            const f3 slj = mk(sh.WO[j][3], sh.WO[j][4], sh.WO[j][5]);
+            const f3 wj = mk(sh.wo(j)[0], sh.wo(j)[1], sh.wo(j)[2]);
+            const f3 slj = mk(sh.wo(j)[3], sh.wo(j)[4], sh.wo(j)[5]);
             float val = dot3(wj, Fcb.a) + dot3(slj, Fcb.l);
             if (j == b) val += dt * ba;
             Ml[d * MST + dj] = val;
@@ -1390,15 +1465,14 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     }
     wave_sync();
     float Mi[S][NVC];
-    float cS[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int d = lane + 16 * s;
       const int dr = d < NVC ? d : 0;
 #pragma unroll
       for (int j = 0; j < NVC; ++j) Mi[s][j] = sh.A[dr * MST + j];
-      cS[s] = (d < nv) ? sh.cvec[d] : 0.f;
     }
+    wave_sync();  // the dense sweep's broadcast buffers overwrite the area
 
     if constexpr (TREE) {
       // ===================================================================
@@ -1647,10 +1721,10 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           cb_hi[s] = d < NVC ? d + NVC : NVC + d;
         }
   #pragma unroll
-        for (int s = 0; s < S; ++s) { sh.cb[0][cb_lo[s]] = Mi[s][0]; sh.cb[0][cb_hi[s]] = Mi[s][0]; }
+        for (int s = 0; s < S; ++s) { sh.cb(0)[cb_lo[s]] = Mi[s][0]; sh.cb(0)[cb_hi[s]] = Mi[s][0]; }
         wave_sync();
   #pragma unroll
-        for (int j = 0; j < NVC; ++j) ckA[j] = sh.cb[0][j];
+        for (int j = 0; j < NVC; ++j) ckA[j] = sh.cb(0)[j];
         auto pivot_step = [&](int k, const float (&ck)[NVC], float (&nck)[NVC]) {
           const float pinv = recip(ck[0]);
           float f[S];
@@ -1662,7 +1736,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           }
   #pragma unroll
           for (int s = 0; s < S; ++s) Mi[s][0] = fmaf(-f[s], ck[1], Mi[s][1]);
-          float* cbn = sh.cb[(k + 1) & 1];
+          float* cbn = sh.cb((k + 1) & 1);
   #pragma unroll
           for (int s = 0; s < S; ++s) { cbn[cb_lo[s]] = Mi[s][0]; cbn[cb_hi[s]] = Mi[s][0]; }
           wave_sync();
@@ -1706,12 +1780,17 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       wave_sync();
   #pragma unroll
       for (int s = 0; s < S; ++s) {
-        const int dr = (lane + 16 * s) < NVC ? lane + 16 * s : 0;
+        // stored column j is original column (nv + j) mod NVC: column c < nv
+        // is at NVC - nv + c.  The read runs on past the row for c >= nv, into
+        // the next row's finite entries, which only ever meet a zero operand
+        // (padding DoFs have no right-hand side and no contact row), and a
+        // padding row reads row 0: its velocity is never used.  Reading every
+        // column from its own wrapped position would hold an address register
+        // per column and slot.
+        const int dr = (lane + 16 * s) < nv ? lane + 16 * s : 0;
+        const float* row = &sh.A[dr * MST + (NVC - nv)];
   #pragma unroll
-        for (int c = 0; c < NVC; ++c) {
-          const int j = c - nv + (c < nv ? NVC : 0);  // register column of original column c
-          Mi[s][c] = sh.A[dr * MST + j];
-        }
+        for (int c = 0; c < NVC; ++c) Mi[s][c] = row[c];
       }
     }
     // the negated inverse in LDS: rotated columns after the sweep, natural
@@ -1731,13 +1810,13 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     // 4. control and free velocity
     // =====================================================================
     const double tk = (double)kstep * dtd;
-    float aS[S], nrhs[S];
+    float aS[S], rhsS[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int d = lane + 16 * s;
       const bool hinge = d >= r0 && d < nvr;
       const int b = hinge ? d - r0 + 1 : 0;
-      const float* rec = bodyv + (size_t)b * BW_WORDS;
+      const float* rec = body_rec(b);
       double ph = (double)rec[BW_CPG + 1] * tk + (double)rec[BW_CPG + 2];
       ph -= 6.283185307179586 * floor(ph * 0.15915494309189535);
       float sph, cph;
@@ -1747,12 +1826,16 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       float rhs = -dt * cS[s];
       if (hinge) rhs += dt * (aS[s] - ba * vS[s]);
       if (d >= nv) rhs = 0.f;
-      nrhs[s] = -rhs;  // sign of the held inverse
+      rhsS[s] = rhs;
     }
     float vp[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) vp[s] = vS[s];
-    matvec_bcast1<S, NVC>(Mi, nrhs, vp);
+    matvec_bcast1<S, NVC>(Mi, rhsS, vp);
+    // formed here, not sunk below the contact rows (its operands would stay in
+    // registers through them)
+#pragma unroll
+    for (int s = 0; s < S; ++s) asm volatile("" : "+v"(vp[s]));
 
     // =====================================================================
     // 5. contact rows
@@ -1773,9 +1856,9 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       } else if (d < nvr) {
         const int b = d - r0 + 1;
         bodyOfDof[s] = b;
-        ang[s] = mk(sh.WO[b][0], sh.WO[b][1], sh.WO[b][2]);
+        ang[s] = mk(sh.wo(b)[0], sh.wo(b)[1], sh.wo(b)[2]);
         // w x (x - o) = w x x + (o - p0) x w + p0 x w
-        cst[s] = (mk(0.f, 0.f, 0.f) - cross3(ang[s], P0)) + mk(sh.WO[b][3], sh.WO[b][4], sh.WO[b][5]);
+        cst[s] = (mk(0.f, 0.f, 0.f) - cross3(ang[s], P0)) + mk(sh.wo(b)[3], sh.wo(b)[4], sh.wo(b)[5]);
       } else if (BALL && d < nv) {
         // ball: spin e_k gives e_k x (x - cb), centre velocity e_k gives e_k
         const int k = d - nvr;
@@ -1788,15 +1871,44 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         cst[s] = mk(0.f, 0.f, 0.f);
       }
     }
+    // contacts beyond the register budget: rows and scalars go to the workspace
+    // (built first, while no contact's rows are held in registers).
+    // Each lane stores and later reloads only values it computed itself (the
+    // scalars are identical in all lanes), so no cross-lane visibility is needed.
+    for (int c = NCR; c < nc; ++c) {
+      const float* e = ovf_entry(c);
+      const f3 x = mk(e[CL_X], e[CL_X + 1], e[CL_X + 2]);
+      const unsigned anc = __float_as_uint(e[CL_ANC]);
+      float Jn[S], Jx[S], Jy[S], Wn[S], Wx[S], Wy[S], scal[10];
+      if constexpr (GEN) {
+        const int kind = (int)e[CL_KIND];
+        build_rows_gen<S, NVC>(Mi, ang, cst, bodyOfDof, x, mk(e[CL_N], e[CL_N + 1], e[CL_N + 2]), e[CL_DEPTH], anc,
+                               __float_as_uint(e[CL_MINUS]), kind == 1 || kind == 2, kind == 3, kc, kb, dt, Jn, Jx,
+                               Jy, Wn, Wx, Wy, scal);
+      }
+      else
+        build_rows<S, NVC>(Mi, ang, cst, bodyOfDof, lane, x, anc, kc, kb, dt, Jn, Jx, Jy, Wn, Wx, Wy, scal);
+      float* rows = ovf_row(c);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int d = lane + 16 * s;
+        if (d < NVC) {
+          rows[0 * NVC + d] = Jn[s]; rows[1 * NVC + d] = Jx[s]; rows[2 * NVC + d] = Jy[s];
+          rows[3 * NVC + d] = Wn[s]; rows[4 * NVC + d] = Wx[s]; rows[5 * NVC + d] = Wy[s];
+        }
+      }
+      float* sd = ovf_scalars(c);
+#pragma unroll
+      for (int i = 0; i < 10; ++i) sd[i] = scal[i];
+    }
+    wave_sync();  // hinge motions read; their area takes the solver scalars
     float JnR[NCR][S], JxR[NCR][S], JyR[NCR][S], WnR[NCR][S], WxR[NCR][S], WyR[NCR][S];
-    // The contacts' solver scalars and multipliers: in registers for the
-    // single-wave families of 20 DoFs and more with at most 8 contacts in
-    // registers (above 256 registers anyway, with room left below 512; their
-    // sweeps would otherwise wait on an LDS read at every contact), else in
-    // LDS: the smaller families fit 256 registers and run two waves per SIMD,
-    // which the 80 more registers would cost them.
-    constexpr bool SREG = WavesPerSimd<NVC, SB, NCR>::value == 1 && NVC >= 20 && NCR <= 8;
-    float scR[SREG ? NCR : 1][10];
+    // the multipliers start at zero: cleared for all contacts at once
+    {
+      float4* z4 = reinterpret_cast<float4*>(sh.scal(0));  // 16-byte aligned, 12 words a contact
+      for (int e = lane; e < NCR * 3; e += 16) z4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    wave_sync();
 #pragma unroll
     for (int c = 0; c < NCR; ++c) {
       if (c < nc) {
@@ -1813,52 +1925,15 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           build_rows<S, NVC>(Mi, ang, cst, bodyOfDof, lane, x, anc, kc, kb, dt, JnR[c], JxR[c], JyR[c], WnR[c],
                              WxR[c], WyR[c], scal);
 #pragma unroll
-        for (int i = 0; i < 10; ++i) {
-          if constexpr (SREG) scR[c][i] = scal[i];
-          else sh.cs[c][i] = scal[i];  // identical in every lane
-        }
+        for (int i = 0; i < 7; ++i) sh.scal(c)[i] = scal[i];  // identical in every lane
       } else {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           JnR[c][s] = JxR[c][s] = JyR[c][s] = 0.f;
           WnR[c][s] = WxR[c][s] = WyR[c][s] = 0.f;
         }
-        if constexpr (SREG) {
-#pragma unroll
-          for (int i = 0; i < 10; ++i) scR[c][i] = 0.f;
-        }
       }
     }
-    // contacts beyond the register budget: rows and scalars go to the workspace.
-    // Each lane stores and later reloads only values it computed itself (the
-    // scalars are identical in all lanes), so no cross-lane visibility is needed.
-    for (int c = NCR; c < nc; ++c) {
-      const float* e = &ovf_list[c * CLW];
-      const f3 x = mk(e[CL_X], e[CL_X + 1], e[CL_X + 2]);
-      const unsigned anc = __float_as_uint(e[CL_ANC]);
-      float Jn[S], Jx[S], Jy[S], Wn[S], Wx[S], Wy[S], scal[10];
-      if constexpr (GEN) {
-        const int kind = (int)e[CL_KIND];
-        build_rows_gen<S, NVC>(Mi, ang, cst, bodyOfDof, x, mk(e[CL_N], e[CL_N + 1], e[CL_N + 2]), e[CL_DEPTH], anc,
-                               __float_as_uint(e[CL_MINUS]), kind == 1 || kind == 2, kind == 3, kc, kb, dt, Jn, Jx,
-                               Jy, Wn, Wx, Wy, scal);
-      }
-      else
-        build_rows<S, NVC>(Mi, ang, cst, bodyOfDof, lane, x, anc, kc, kb, dt, Jn, Jx, Jy, Wn, Wx, Wy, scal);
-      float* rows = ovf_rows + (size_t)c * 6 * NVC;
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int d = lane + 16 * s;
-        if (d < NVC) {
-          rows[0 * NVC + d] = Jn[s]; rows[1 * NVC + d] = Jx[s]; rows[2 * NVC + d] = Jy[s];
-          rows[3 * NVC + d] = Wn[s]; rows[4 * NVC + d] = Wx[s]; rows[5 * NVC + d] = Wy[s];
-        }
-      }
-      float* sd = ovf_scal + (size_t)c * kOvfScal;
-#pragma unroll
-      for (int i = 0; i < 10; ++i) sd[i] = scal[i];
-    }
-
     // =====================================================================
     // 6. projected Gauss-Seidel
     // =====================================================================
@@ -1922,18 +1997,14 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
         if (c < nc) {
           float sc[10], lam[3];
 #pragma unroll
-          for (int i = 0; i < 10; ++i) sc[i] = SREG ? scR[c][i] : sh.cs[c][i];
+          for (int i = 0; i < 10; ++i) sc[i] = sh.scal(c)[i];
           lam[0] = sc[7]; lam[1] = sc[8]; lam[2] = sc[9];
           contact_row<S>(vp, JnR[c], JxR[c], JyR[c], WnR[c], WxR[c], WyR[c], sc, lam, mu, dt);
-          if constexpr (SREG) {
-            scR[c][7] = lam[0]; scR[c][8] = lam[1]; scR[c][9] = lam[2];
-          } else {
-            sh.cs[c][7] = lam[0]; sh.cs[c][8] = lam[1]; sh.cs[c][9] = lam[2];
-          }
+          sh.scal(c)[7] = lam[0]; sh.scal(c)[8] = lam[1]; sh.scal(c)[9] = lam[2];
         }
       }
       for (int c = NCR; c < nc; ++c) {
-        const float* rows = ovf_rows + (size_t)c * 6 * NVC;
+        const float* rows = ovf_row(c);
         float Jn[S], Jx[S], Jy[S], Wn[S], Wx[S], Wy[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -1943,7 +2014,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           Jy[s] = ok ? rows[2 * NVC + d] : 0.f; Wn[s] = ok ? rows[3 * NVC + d] : 0.f;
           Wx[s] = ok ? rows[4 * NVC + d] : 0.f; Wy[s] = ok ? rows[5 * NVC + d] : 0.f;
         }
-        float* sd = ovf_scal + (size_t)c * kOvfScal;
+        float* sd = ovf_scalars(c);
         float sc[10], lam[3];
 #pragma unroll
         for (int i = 0; i < 10; ++i) sc[i] = sd[i];
@@ -1970,7 +2041,11 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     }
     float p0n[3] = {p0[0], p0[1], p0[2]}, Q0n[4] = {Q0[0], Q0[1], Q0[2], Q0[3]};
     if (r0 == 6) {
-      const f3 dp = mul(R0, vn);
+      // the root rotation formed again from its quaternion (the same products):
+      // held since the forward pass it would take nine registers all along
+      float Qr[4] = {Q0[0], Q0[1], Q0[2], Q0[3]};
+      asm volatile("" : "+v"(Qr[0]), "+v"(Qr[1]), "+v"(Qr[2]), "+v"(Qr[3]));
+      const f3 dp = mul(quat_rot(Qr[0], Qr[1], Qr[2], Qr[3]), vn);
       p0n[0] = fmaf(dt, dp.x, p0[0]); p0n[1] = fmaf(dt, dp.y, p0[1]); p0n[2] = fmaf(dt, dp.z, p0[2]);
       quat_step<true>(Q0n, wn * dt);  // body-frame rate
       bool ok = true;
@@ -1986,11 +2061,11 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const int d = lane + 16 * s;
-        if (d >= nvr && d < nv) sh.cvec[d] = vp[s];
+        if (d >= nvr && d < nv) sh.cvec()[d] = vp[s];
       }
       wave_sync();
-      const f3 wbn = mk(sh.cvec[nvr], sh.cvec[nvr + 1], sh.cvec[nvr + 2]);
-      const f3 vbn = mk(sh.cvec[nvr + 3], sh.cvec[nvr + 4], sh.cvec[nvr + 5]);
+      const f3 wbn = mk(sh.cvec()[nvr], sh.cvec()[nvr + 1], sh.cvec()[nvr + 2]);
+      const f3 vbn = mk(sh.cvec()[nvr + 3], sh.cvec()[nvr + 4], sh.cvec()[nvr + 5]);
       wave_sync();  // read before the next step's writes
       pbn[0] = fmaf(dt, vbn.x, pb[0]); pbn[1] = fmaf(dt, vbn.y, pb[1]); pbn[2] = fmaf(dt, vbn.z, pb[2]);
       // world angular velocity: Q <- exp(dt w) Q
@@ -2019,11 +2094,12 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
 #pragma unroll
     for (int i = 0; i < 4; ++i) Qb[i] = Qbn[i];
     kstep += 1;
-    cnt_contact += (unsigned long long)nc;
-    cnt_clamp += (unsigned long long)clampsum;
+    n_contact += (unsigned)nc;
+    n_clamp += (unsigned)clampsum;
   }
 
   // ---- write back ----
+  asm volatile("" : "+v"(vid), "+v"(lane));  // its addresses are formed here, not before the loop
   {
     float* qdst = a.q + (size_t)vid * kQStride;
     float* vdst = a.v + (size_t)vid * kVStride;
@@ -2048,14 +2124,14 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       a.status[vid] = status;
       const float dx = p0[0] - a.xy0[2 * vid], dy = p0[1] - a.xy0[2 * vid + 1];
       a.fit[vid] = status ? __int_as_float(0x7fc00000) : ((r0 == 6) ? sqrtf(dx * dx + dy * dy) : 0.f);
-      a.cnt[2 * vid] = cnt_contact;
-      a.cnt[2 * vid + 1] = cnt_clamp;
+      a.cnt[2 * vid] = (a.reset ? 0ull : a.cnt[2 * vid]) + n_contact;
+      a.cnt[2 * vid + 1] = (a.reset ? 0ull : a.cnt[2 * vid + 1]) + n_clamp;
     }
   }
 }
 
 template <int NVC, int SB, int NCR, bool BALL = false, bool SELF = false, bool TREE = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WavesPerSimd<NVC, SB, NCR>::value)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WavesPerSimd<NVC, SB, NCR, BALL, SELF, TREE>::value)))
 void rollout_kernel(BinArgs a, ModelParams P) {
   __shared__ GroupLds<NVC, SB, NCR, BALL, SELF, TREE> lds_all[kVarPerWave];
   rollout_body<NVC, SB, NCR, BALL, SELF, TREE>(a, P, blockIdx.x, lds_all);

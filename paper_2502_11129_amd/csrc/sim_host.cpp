@@ -366,7 +366,7 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
     if (!cap_or_zero(o.slots32_min_nvc)) return bad("slots32_min_nvc must be 0 or a DoF capacity 8, 12, ..., 28");
     for (int k = 0; k < 6; ++k)
       if (o.ncr_by_nvc[k] < 0) return bad("ncr_by_nvc entries must be >= 0");
-    hp->steps_per_launch = o.steps_per_launch > 0 ? o.steps_per_launch : kStepsPerLaunch;
+    hp->steps_per_launch = o.steps_per_launch > 0 ? std::min(o.steps_per_launch, kMaxStepsPerLaunch) : kStepsPerLaunch;
   }
   const int n = d->n_variants;
   hp->n = n;

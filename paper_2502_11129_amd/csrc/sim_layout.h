@@ -48,6 +48,10 @@ constexpr int kMaxSelfContacts = 256;
 // Overflow scratch per contact (contacts that do not fit in registers).
 constexpr int kOvfScal = 12;     // per-contact solver scalars
 
+// Steps of one launch at most: a launch counts its contact and clamp rows in
+// 32 bits (at most 8 * 32 + 33 + 256 contacts a step).
+constexpr int kMaxStepsPerLaunch = 1 << 20;
+
 struct ModelParams {
   float kp, kd, tau_max, k_contact, b_contact, dt;
   float g[3];

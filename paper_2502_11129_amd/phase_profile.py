@@ -71,7 +71,7 @@ def instrument(src: str) -> str:
     # projected Gauss-Seidel: clamp rows, contacts in registers, overflow
     # contacts, summed over the sweeps
     pgs = ("      // (i) actuator clamp rows in hinge order.", "      // (ii) contact rows in (body, corner) order",
-           "      for (int c = NCR; c < nc; ++c) {\n        const float* rows = ovf_rows")
+           "      for (int c = NCR; c < nc; ++c) {\n        const float* rows = ovf_row")
     for k, anchor in enumerate(pgs):
         if s.count(anchor) != 1:
             raise RuntimeError(f"projected Gauss-Seidel mark {k} not found")
