@@ -300,75 +300,119 @@ struct alignas(16) GroupLds {
 // Builds J (normal z, tangents x, y) of the point x for the lane's DoF slots,
 // W = M~^-1 J^T, the row denominators and cross terms, and the solver scalars.
 // ----------------------------------------------------------------------------
-// Column C of three mat-vecs with the held (negated) inverse: y_k[s] -=
-// Mi[s][C] * x_k(DoF C), with x_k(DoF C) read from lane C mod 16 of the row and
-// its sign turned by the multiply-add itself (v_fmac_f32 with a negated
-// row_newbcast DPP source), so neither costs a separate instruction or
-// register.  Same single rounding as fmaf(Mi, -x, y).  The leading s_nop
-// gives the two wait states a DPP source needs after a VALU write, which the
-// compiler does not track across inline assembly.  Every lane of an active row
-// takes part (row-uniform control flow), as DPP reads require.
+// Four columns C..C + 3 of three mat-vecs with the held (negated) inverse: y_k[s]
+// -= Mi[s][c] * x_k(DoF c) for each in turn, with x_k(DoF c) read from lane c mod
+// 16 of the row and its sign turned by the multiply-add itself (v_fmac_f32 with
+// a negated row_newbcast DPP source), so neither costs a separate instruction or
+// register.  Same single rounding as fmaf(Mi, -x, y).  The leading s_nop gives
+// the two wait states a DPP source needs after a VALU write, which the compiler
+// does not track across inline assembly; one serves four columns (every s_nop is
+// an issue slot of its own: one a column was 39 of a contact's 316 instructions).
+// Every lane of an active row takes part (row-uniform control flow), as DPP
+// reads require.
 template <int L>
-__device__ __forceinline__ void fmac3_bcast(const float (&m)[1], float xa, float xb, float xc, float (&ya)[1],
-                                            float (&yb)[1], float (&yc)[1]) {
+__device__ __forceinline__ void fmac3_bcast(const float (&m0)[1], const float (&m1)[1], const float (&m2)[1], const float (&m3)[1], float xa, float xb,
+                                            float xc, float (&ya)[1], float (&yb)[1], float (&yc)[1]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, -%3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, -%4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %2, -%5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%3, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%5, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%5, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%3, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%3, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%4, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0]), "+v"(yb[0]), "+v"(yc[0])
-      : "v"(xa), "v"(xb), "v"(xc), "v"(m[0]), "n"(L));
+      : "v"(xa), "v"(xb), "v"(xc), "v"(m0[0]), "v"(m1[0]), "v"(m2[0]), "v"(m3[0]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 template <int L>
-__device__ __forceinline__ void fmac3_bcast(const float (&m)[2], float xa, float xb, float xc, float (&ya)[2],
-                                            float (&yb)[2], float (&yc)[2]) {
+__device__ __forceinline__ void fmac3_bcast(const float (&m0)[2], const float (&m1)[2], const float (&m2)[2], const float (&m3)[2], float xa, float xb,
+                                            float xc, float (&ya)[2], float (&yb)[2], float (&yc)[2]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, -%6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, -%6, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %2, -%7, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %3, -%7, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %4, -%8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %5, -%8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%6, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%6, %10 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%7, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, -%7, %10 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, -%8, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, -%8, %10 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%6, %11 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%6, %12 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%7, %11 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, -%7, %12 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, -%8, %11 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, -%8, %12 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%6, %13 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%6, %14 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%7, %13 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, -%7, %14 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, -%8, %13 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, -%8, %14 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%6, %15 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%6, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, -%7, %15 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, -%7, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %4, -%8, %15 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, -%8, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0]), "+v"(ya[1]), "+v"(yb[0]), "+v"(yb[1]), "+v"(yc[0]), "+v"(yc[1])
-      : "v"(xa), "v"(xb), "v"(xc), "v"(m[0]), "v"(m[1]), "n"(L));
+      : "v"(xa), "v"(xb), "v"(xc), "v"(m0[0]), "v"(m0[1]), "v"(m1[0]), "v"(m1[1]), "v"(m2[0]), "v"(m2[1]), "v"(m3[0]), "v"(m3[1]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 
 template <int S, int NVC, int C = 0>
 __device__ __forceinline__ void matvec_bcast3(const float (&Mi)[S][NVC], const float (&a)[S], const float (&b)[S],
                                               const float (&c)[S], float (&ya)[S], float (&yb)[S], float (&yc)[S]) {
   static_assert(S == 1 || S == 2, "at most 32 DoF slots per variant");
+  static_assert(NVC % 4 == 0, "columns are taken in fours");
   if constexpr (C < NVC) {
-    float m[S];
+    float m[4][S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) m[s] = Mi[s][C];
-    fmac3_bcast<C % 16>(m, a[C / 16], b[C / 16], c[C / 16], ya, yb, yc);
-    matvec_bcast3<S, NVC, C + 1>(Mi, a, b, c, ya, yb, yc);
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int s = 0; s < S; ++s) m[j][s] = Mi[s][C + j];
+    fmac3_bcast<C % 16>(m[0], m[1], m[2], m[3], a[C / 16], b[C / 16], c[C / 16], ya, yb, yc);
+    matvec_bcast3<S, NVC, C + 4>(Mi, a, b, c, ya, yb, yc);
   }
 }
 
-// The same for one mat-vec, y[s] -= Mi[s][C] * x(DoF C).
+// The same for one mat-vec.
 template <int L>
-__device__ __forceinline__ void fmac1_bcast(const float (&m)[1], float xa, float (&ya)[1]) {
+__device__ __forceinline__ void fmac1_bcast(const float (&m0)[1], const float (&m1)[1], const float (&m2)[1], const float (&m3)[1], float xa, float (&ya)[1]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0])
-      : "v"(xa), "v"(m[0]), "n"(L));
+      : "v"(xa), "v"(m0[0]), "v"(m1[0]), "v"(m2[0]), "v"(m3[0]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 template <int L>
-__device__ __forceinline__ void fmac1_bcast(const float (&m)[2], float xa, float (&ya)[2]) {
+__device__ __forceinline__ void fmac1_bcast(const float (&m0)[2], const float (&m1)[2], const float (&m2)[2], const float (&m3)[2], float xa, float (&ya)[2]) {
   asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, -%2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, -%2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      "v_fmac_f32_dpp %0, -%2, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%2, %4 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%2, %5 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%2, %6 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%2, %7 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%2, %8 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, -%2, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, -%2, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
       : "+v"(ya[0]), "+v"(ya[1])
-      : "v"(xa), "v"(m[0]), "v"(m[1]), "n"(L));
+      : "v"(xa), "v"(m0[0]), "v"(m0[1]), "v"(m1[0]), "v"(m1[1]), "v"(m2[0]), "v"(m2[1]), "v"(m3[0]), "v"(m3[1]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
+
 template <int S, int NVC, int C = 0>
 __device__ __forceinline__ void matvec_bcast1(const float (&Mi)[S][NVC], const float (&a)[S], float (&ya)[S]) {
   if constexpr (C < NVC) {
-    float m[S];
+    float m[4][S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) m[s] = Mi[s][C];
-    fmac1_bcast<C % 16>(m, a[C / 16], ya);
-    matvec_bcast1<S, NVC, C + 1>(Mi, a, ya);
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int s = 0; s < S; ++s) m[j][s] = Mi[s][C + j];
+    fmac1_bcast<C % 16>(m[0], m[1], m[2], m[3], a[C / 16], ya);
+    matvec_bcast1<S, NVC, C + 4>(Mi, a, ya);
   }
 }
 
@@ -379,10 +423,11 @@ __device__ __forceinline__ void matvec_bcast1(const float (&Mi)[S][NVC], const f
 //   [0] k d s1, [1] kb s1, [2] kb s1 dt D_n   (normal row)
 //   [3] s5 dt D_xn, [4] s6 dt D_yn            (tangential change per normal change)
 //   [5] s5, [6] s6
-//   [7..9] lambda_n, lambda_x, lambda_y       (cold start)
+// (in memory a contact has 12 words: these, then at 8..10 the multipliers
+// lambda_n, lambda_x, lambda_y, 16-byte aligned, zero at the cold start)
 // guard: a self-contact row no DoF can move (D < 1e-9) is inert, its gains 0.
 __device__ __forceinline__ void solver_scalars(float kd, float Dn, float Dx, float Dy, float Dxn, float Dyn,
-                                               float kb, float dt, bool guard, float (&scal)[10]) {
+                                               float kb, float dt, bool guard, float (&scal)[7]) {
   float s1 = recip(Dn * (1.f + kb * dt));
   float s5 = recip(dt * Dx), s6 = recip(dt * Dy);
   if (guard) {
@@ -398,16 +443,13 @@ __device__ __forceinline__ void solver_scalars(float kd, float Dn, float Dx, flo
   scal[4] = s6 * (dt * Dyn);
   scal[5] = s5;
   scal[6] = s6;
-  scal[7] = 0.f;
-  scal[8] = 0.f;
-  scal[9] = 0.f;
 }
 
 template <int S, int NVC>
 __device__ __forceinline__ void build_rows(const float (&Mi)[S][NVC], const f3 (&ang)[S], const f3 (&cst)[S],
                                            const int (&bodyOfDof)[S], int lane, f3 x, unsigned anc, float kc,
                                            float kb, float dt, float (&Jn)[S], float (&Jx)[S], float (&Jy)[S],
-                                           float (&Wn)[S], float (&Wx)[S], float (&Wy)[S], float (&scal)[10]) {
+                                           float (&Wn)[S], float (&Wx)[S], float (&Wy)[S], float (&scal)[7]) {
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const bool on = (bodyOfDof[s] < 0) || ((anc >> bodyOfDof[s]) & 1u);
@@ -453,7 +495,7 @@ __device__ __forceinline__ void build_rows_gen(const float (&Mi)[S][NVC], const 
                                                const int (&bodyOfDof)[S], f3 x, f3 n, float depth, unsigned plus,
                                                unsigned minus, bool ball, bool guard, float kc, float kb, float dt,
                                                float (&Jn)[S], float (&Jx)[S], float (&Jy)[S], float (&Wn)[S],
-                                               float (&Wx)[S], float (&Wy)[S], float (&scal)[10]) {
+                                               float (&Wx)[S], float (&Wy)[S], float (&scal)[7]) {
   f3 t1, t2;
   tangents(n, t1, t2);
 #pragma unroll
@@ -542,6 +584,23 @@ __device__ __forceinline__ f3 sat_axis(f3 pP, const m33& RP, f3 hP, f3 pQ, const
       consider(c * (1.f / sqrtf(n2)));
     }
   return dot3(best, d) < 0.f ? best * -1.f : best;
+}
+
+// Boxes P and Q apart along a face normal of either by more than 1e-5 m plus
+// 1e-5 of their reach along it and 2e-6 of the coordinates' size (float rounding
+// of the overlap and of a corner's position is near 1e-7 of these): neither
+// sat_axis' least overlap nor a corner's side can come out otherwise.
+__device__ __forceinline__ bool boxes_apart(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ) {
+  const f3 d = pP - pQ;
+  const float slack = 1e-5f + 2e-6f * (fabsf(pP.x) + fabsf(pP.y) + fabsf(pP.z));
+  bool apart = false;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const f3 u = k < 3 ? mcol(RP, k) : mcol(RQ, k - 3);
+    const float reach = box_radius(RP, hP, u) + box_radius(RQ, hQ, u);
+    apart = apart || fabsf(dot3(u, d)) - reach > slack + 1e-5f * reach;
+  }
+  return apart;
 }
 
 // An edge pair takes the contact from the face axes only when its overlap
@@ -761,7 +820,7 @@ __device__ __forceinline__ bool sphere_box(f3 c, float r, f3 p, const m33& R, f3
 template <int S>
 __device__ __forceinline__ void contact_row(float (&vp)[S], const float (&Jn)[S], const float (&Jx)[S],
                                             const float (&Jy)[S], const float (&Wn)[S], const float (&Wx)[S],
-                                            const float (&Wy)[S], const float (&sc)[10], float (&lam)[3],
+                                            const float (&Wy)[S], const float (&sc)[7], float (&lam)[3],
                                             float mu, float dt) {
   float pn = 0.f, px = 0.f, py = 0.f;
 #pragma unroll
@@ -770,9 +829,12 @@ __device__ __forceinline__ void contact_row(float (&vp)[S], const float (&Jn)[S]
     px = fmaf(Jx[s], vp[s], px);
     py = fmaf(Jy[s], vp[s], py);
   }
+  const float un = row_sum(pn), ux = row_sum(px), uy = row_sum(py);
+  // the contact's scalars are on their way from LDS meanwhile: nothing that
+  // needs them may be scheduled before the sums
+  __builtin_amdgcn_sched_barrier(0);
   const float ln0 = lam[0], lx0 = lam[1], ly0 = lam[2];
   const float c0 = fmaf(sc[2], ln0, sc[0]);
-  const float un = row_sum(pn), ux = row_sum(px), uy = row_sum(py);
   const float gxp = fmaf(-sc[5], ux, lx0), gyp = fmaf(-sc[6], uy, ly0);
   const float ln = fmaxf(0.f, fmaf(-sc[1], un, c0));
   const float dn = ln - ln0;
@@ -802,7 +864,7 @@ __device__ __forceinline__ int row_min_i(int x) {
 // ----------------------------------------------------------------------------
 // The kernel.
 // ----------------------------------------------------------------------------
-// Waves per SIMD, i.e. the register budget (512, 256, 168 or 128 a wave).  A
+// Waves per SIMD, i.e. the register budget (512, 256 or 168 a wave).  A
 // wave alone on a SIMD issues one instruction of any kind in four cycles,
 // while two together issue an FMA, add, multiply or move in about two each
 // (DPP, compares, selects and scalar operands in four): measured on gfx950.
@@ -820,8 +882,7 @@ template <int NVC, int SB, int NCR, bool BALL, bool SELF, bool TREE>
 struct WavesPerSimd {
   static constexpr int value = TREE || NCR > 8 && NVC > 16 || BALL && NVC > 24 ? 1
                                : NVC > 16 || NCR > 8                          ? 2
-                               : BALL || SELF || NVC <= 12                    ? 3
-                                                                              : 4;
+                                                                              : 3;
 };
 
 // One workgroup (one wave, four variants) of a bin: `block` is the
@@ -1002,6 +1063,22 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     const m33 R0 = quat_rot(Q0[0], Q0[1], Q0[2], Q0[3]);
     const f3 P0 = mk(p0[0], p0[1], p0[2]);
     wave_sync();
+    // every hinge's rotation relative to its parent needs no other body: formed
+    // for all bodies at once, off the level chain, where the rotation will stand
+#pragma unroll
+    for (int t = 0; t < SB; ++t) {
+      const int b = lane + 16 * t;
+      if (b >= 1 && b < nb) {
+        const float* rec = body_rec(b);
+        const int dof = r0 + b - 1;
+        const m33 E = matmul(quat_rot(rec[BW_RQ], rec[BW_RQ + 1], rec[BW_RQ + 2], rec[BW_RQ + 3]),
+                             axis_rot_acc(mk(rec[BW_AXIS], rec[BW_AXIS + 1], rec[BW_AXIS + 2]), sh.sth()[dof],
+                                          sh.cth()[dof]));
+#pragma unroll
+        for (int k2 = 0; k2 < 9; ++k2) sh.A[b * 24 + k2] = E.m[k2];
+      }
+    }
+    wave_sync();
 
     for (int lev = 0; lev <= maxdepth; ++lev) {
       const int i1 = sh.ls[lev + 1];
@@ -1029,10 +1106,11 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           const sv Vl = {mk(pr[12], pr[13], pr[14]), mk(pr[15], pr[16], pr[17])};
           const sv Al = {mk(pr[18], pr[19], pr[20]), mk(pr[21], pr[22], pr[23])};
           const int dof = r0 + b - 1;
-          const float sn = sh.sth()[dof], cs = sh.cth()[dof], thd = sh.thd()[dof];
+          const float thd = sh.thd()[dof];
           const f3 u = mk(rec[BW_AXIS], rec[BW_AXIS + 1], rec[BW_AXIS + 2]);
-          const m33 E = matmul(quat_rot(rec[BW_RQ], rec[BW_RQ + 1], rec[BW_RQ + 2], rec[BW_RQ + 3]),
-                               axis_rot_acc(u, sn, cs));
+          m33 E;
+#pragma unroll
+          for (int k2 = 0; k2 < 9; ++k2) E.m[k2] = sh.A[b * 24 + k2];
           R = matmul(Rl, E);
           o = pl + mul(Rl, mk(rec[BW_AP], rec[BW_AP + 1], rec[BW_AP + 2]));
           p = o - mul(R, mk(rec[BW_AC], rec[BW_AC + 1], rec[BW_AC + 2]));
@@ -1087,28 +1165,31 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       }
 #pragma unroll
       for (int t = 0; t < SB; ++t) {
-        const int b = lane + 16 * t;
-        if (b < nb) {
-          const unsigned msk = mskS[t];
-          if (msk) {
-            const float* pr = &sh.A[b * 24];
-            const float* rec = body_rec(b);
-            const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
-            const unsigned anc = __float_as_uint(rec[BW_ANCESTORS]);
-            int idx = off[t];
-            for (int cn = 0; cn < 8; ++cn) {
-              if (msk & (1u << cn)) {
-                const f3 sv3 = mk((cn & 1) ? h.x : -h.x, (cn & 2) ? h.y : -h.y, (cn & 4) ? h.z : -h.z);
-                const f3 x = mk(pr[9] + pr[0] * sv3.x + pr[1] * sv3.y + pr[2] * sv3.z,
-                                pr[10] + pr[3] * sv3.x + pr[4] * sv3.y + pr[5] * sv3.z,
-                                pr[11] + pr[6] * sv3.x + pr[7] * sv3.y + pr[8] * sv3.z);
-                const f3 up = mk(0.f, 0.f, 1.f);
-                if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, anc, 0u, up, -x.z, 0);
-                else put_contact<GEN>(ovf_entry(idx), x, anc, 0u, up, -x.z, 0);
-                ++idx;
-              }
-            }
-          }
+        unsigned msk = mskS[t];
+        // one active corner of every lane's body per turn (most bodies have
+        // none, a few two or four), the pose read once
+        if (msk) {
+          const int b = lane + 16 * t;
+          const float* pr = &sh.A[b * 24];
+          const float* rec = body_rec(b);
+          const f3 h = mk(rec[BW_HALF], rec[BW_HALF + 1], rec[BW_HALF + 2]);
+          const unsigned anc = __float_as_uint(rec[BW_ANCESTORS]);
+          float pose[12];
+#pragma unroll
+          for (int k2 = 0; k2 < 12; ++k2) pose[k2] = pr[k2];
+          int idx = off[t];
+          do {
+            const int cn = __builtin_ctz(msk);
+            msk &= msk - 1u;
+            const f3 sv3 = mk((cn & 1) ? h.x : -h.x, (cn & 2) ? h.y : -h.y, (cn & 4) ? h.z : -h.z);
+            const f3 x = mk(pose[9] + pose[0] * sv3.x + pose[1] * sv3.y + pose[2] * sv3.z,
+                            pose[10] + pose[3] * sv3.x + pose[4] * sv3.y + pose[5] * sv3.z,
+                            pose[11] + pose[6] * sv3.x + pose[7] * sv3.y + pose[8] * sv3.z);
+            const f3 up = mk(0.f, 0.f, 1.f);
+            if (idx < NCR) put_contact<GEN>(&sh.cl[idx][0], x, anc, 0u, up, -x.z, 0);
+            else put_contact<GEN>(ovf_entry(idx), x, anc, 0u, up, -x.z, 0);
+            ++idx;
+          } while (msk);
         }
       }
     }
@@ -1118,12 +1199,15 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       // candidates are compacted in pair order (conservative test: every
       // corner hit passes it)
       int ncand = 0;
+      float2 next = make_float2(0.f, 0.f);  // the table is read one turn ahead
+      if (lane < npairs) next = *reinterpret_cast<const float2*>(pair_rec(lane));
       for (int k0 = 0; k0 < npairs; k0 += 16) {
         const int k = k0 + lane;
         int cand = 0;
         int pr = 0;
+        const float2 pe = next;
+        if (k + 16 < npairs) next = *reinterpret_cast<const float2*>(pair_rec(k + 16));
         if (k < npairs) {
-          const float2 pe = *reinterpret_cast<const float2*>(pair_rec(k));
           pr = __float_as_int(pe.x);
           const int ia = pr & 0xff, ib = pr >> 8;
           const float* pa = &sh.A[ia * 24];
@@ -1165,21 +1249,27 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           const float* recb = body_rec(ib);
           ha = mk(reca[BW_HALF], reca[BW_HALF + 1], reca[BW_HALF + 2]);
           hb = mk(recb[BW_HALF], recb[BW_HALF + 1], recb[BW_HALF + 2]);
-          for (int c = 0; c < 8; ++c)
-            if (point_in_box(box_corner(Ra, Pa, ha, c), Pb, Rb, hb)) hits |= 1u << c;
-          for (int c = 0; c < 8; ++c)
-            if (point_in_box(box_corner(Rb, Pb, hb, c), Pa, Ra, ha)) hits |= 1u << (8 + c);
-          // no corner inside: two crossing edges, if the boxes intersect there (bit
-          // 16), or else an edge or face through a face (the clipped incident face)
-          if (hits == 0u && edge_contact(Pa, Ra, ha, Pb, Rb, hb, ex, en, ed, face)) hits = 1u << 16;
-          else if (hits == 0u && face >= 0) {
-            FaceClip F;
-            face_setup(Pa, Ra, ha, Pb, Rb, hb, face, F);
+          // Most candidates are apart along a face axis of one of the boxes, by
+          // more than any rounding: no corner is inside then and the least
+          // overlap is negative, so the tests below would find nothing.  When
+          // that holds for every candidate of the wave they are skipped.
+          if (!boxes_apart(Pa, Ra, ha, Pb, Rb, hb)) {
+            for (int c = 0; c < 8; ++c)
+              if (point_in_box(box_corner(Ra, Pa, ha, c), Pb, Rb, hb)) hits |= 1u << c;
+            for (int c = 0; c < 8; ++c)
+              if (point_in_box(box_corner(Rb, Pb, hb, c), Pa, Ra, ha)) hits |= 1u << (8 + c);
+            // no corner inside: two crossing edges, if the boxes intersect there (bit
+            // 16), or else an edge or face through a face (the clipped incident face)
+            if (hits == 0u && edge_contact(Pa, Ra, ha, Pb, Rb, hb, ex, en, ed, face)) hits = 1u << 16;
+            else if (hits == 0u && face >= 0) {
+              FaceClip F;
+              face_setup(Pa, Ra, ha, Pb, Rb, hb, face, F);
 #pragma unroll 1
-            for (int c = 0; c < 24; ++c) {
-              f3 x;
-              float dep;
-              if (face_candidate(F, c, x, dep)) fmask |= 1u << c;
+              for (int c = 0; c < 24; ++c) {
+                f3 x;
+                float dep;
+                if (face_candidate(F, c, x, dep)) fmask |= 1u << c;
+              }
             }
           }
         }
@@ -1879,7 +1969,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       const float* e = ovf_entry(c);
       const f3 x = mk(e[CL_X], e[CL_X + 1], e[CL_X + 2]);
       const unsigned anc = __float_as_uint(e[CL_ANC]);
-      float Jn[S], Jx[S], Jy[S], Wn[S], Wx[S], Wy[S], scal[10];
+      float Jn[S], Jx[S], Jy[S], Wn[S], Wx[S], Wy[S], scal[7];
       if constexpr (GEN) {
         const int kind = (int)e[CL_KIND];
         build_rows_gen<S, NVC>(Mi, ang, cst, bodyOfDof, x, mk(e[CL_N], e[CL_N + 1], e[CL_N + 2]), e[CL_DEPTH], anc,
@@ -1899,7 +1989,8 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       }
       float* sd = ovf_scalars(c);
 #pragma unroll
-      for (int i = 0; i < 10; ++i) sd[i] = scal[i];
+      for (int i = 0; i < 7; ++i) sd[i] = scal[i];
+      sd[8] = sd[9] = sd[10] = 0.f;  // multipliers
     }
     wave_sync();  // hinge motions read; their area takes the solver scalars
     float JnR[NCR][S], JxR[NCR][S], JyR[NCR][S], WnR[NCR][S], WxR[NCR][S], WyR[NCR][S];
@@ -1914,7 +2005,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       if (c < nc) {
         const f3 x = mk(sh.cl[c][CL_X], sh.cl[c][CL_X + 1], sh.cl[c][CL_X + 2]);
         const unsigned anc = __float_as_uint(sh.cl[c][CL_ANC]);
-        float scal[10];
+        float scal[7];
         if constexpr (GEN) {
           const int kind = (int)sh.cl[c][CL_KIND];
           build_rows_gen<S, NVC>(Mi, ang, cst, bodyOfDof, x, mk(sh.cl[c][CL_N], sh.cl[c][CL_N + 1], sh.cl[c][CL_N + 2]),
@@ -1939,9 +2030,11 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
     // =====================================================================
     float Dl[S];    // actuator clamp corrections Delta, held by the DoF's owner lane/slot
     float rden[S];  // 1 / (1 - b_a dt D_jj), fixed for the step
+    bool hingeS[S];  // the DoF has a clamp row (a lane mask in scalar registers)
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       Dl[s] = 0.f;
+      hingeS[s] = lane + 16 * s >= r0 && lane + 16 * s < nvr;
       rden[s] = 1.f / (1.f - ba * dt * Dd[s]);
     }
     constexpr int kNoRow = 1 << 20;
@@ -1951,8 +2044,15 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
       // the old one are no-ops, so only the lowest changing row is applied,
       // and the rest re-evaluated after it: the same result as visiting every
       // row in order.
+      // Most sweeps engage no row: one test over all lanes (a correction held,
+      // or the PD law beyond the limit at the current velocity, which is
+      // nonzero Delta exactly) skips the evaluation.
+      bool engaged = false;
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        engaged = engaged || (hingeS[s] && (Dl[s] != 0.f || fabsf(aS[s] - ba * vp[s]) > tmax));
       int last = -1;  // row-uniform: last hinge DoF applied in this sweep
-      while (true) {
+      while (__builtin_amdgcn_ballot_w64(engaged) != 0) {
         int first = kNoRow;
         float ndv[S];
 #pragma unroll
@@ -1964,7 +2064,7 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           const float over = sv_ > tmax ? sv_ - tmax : (sv_ < -tmax ? sv_ + tmax : 0.f);
           const float nd = over != 0.f ? over * rden[s] : 0.f;
           ndv[s] = nd;
-          if (d >= r0 && d < nvr && d > last && nd != Dl[s]) first = min(first, d);
+          if (hingeS[s] && d > last && nd != Dl[s]) first = min(first, d);
         }
         if (__builtin_amdgcn_ballot_w64(first < kNoRow) == 0) break;  // no row of any variant changes
         first = row_min_i(first);
@@ -1995,12 +2095,14 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
 #pragma unroll
       for (int c = 0; c < NCR; ++c) {
         if (c < nc) {
-          float sc[10], lam[3];
+          float sc[7], lam[3];
+          const float* e = sh.scal(c);
 #pragma unroll
-          for (int i = 0; i < 10; ++i) sc[i] = sh.scal(c)[i];
-          lam[0] = sc[7]; lam[1] = sc[8]; lam[2] = sc[9];
+          for (int i = 0; i < 7; ++i) sc[i] = e[i];
+          lam[0] = e[8]; lam[1] = e[9]; lam[2] = e[10];
           contact_row<S>(vp, JnR[c], JxR[c], JyR[c], WnR[c], WxR[c], WyR[c], sc, lam, mu, dt);
-          sh.scal(c)[7] = lam[0]; sh.scal(c)[8] = lam[1]; sh.scal(c)[9] = lam[2];
+          float* l = sh.scal(c) + 8;
+          l[0] = lam[0]; l[1] = lam[1]; l[2] = lam[2];
         }
       }
       for (int c = NCR; c < nc; ++c) {
@@ -2015,12 +2117,12 @@ __device__ __forceinline__ void rollout_body(const BinArgs& a, const ModelParams
           Wx[s] = ok ? rows[4 * NVC + d] : 0.f; Wy[s] = ok ? rows[5 * NVC + d] : 0.f;
         }
         float* sd = ovf_scalars(c);
-        float sc[10], lam[3];
+        float sc[7], lam[3];
 #pragma unroll
-        for (int i = 0; i < 10; ++i) sc[i] = sd[i];
-        lam[0] = sc[7]; lam[1] = sc[8]; lam[2] = sc[9];
+        for (int i = 0; i < 7; ++i) sc[i] = sd[i];
+        lam[0] = sd[8]; lam[1] = sd[9]; lam[2] = sd[10];
         contact_row<S>(vp, Jn, Jx, Jy, Wn, Wx, Wy, sc, lam, mu, dt);
-        sd[7] = lam[0]; sd[8] = lam[1]; sd[9] = lam[2];
+        sd[8] = lam[0]; sd[9] = lam[1]; sd[10] = lam[2];
       }
     }
 

@@ -78,7 +78,7 @@ def instrument(src: str) -> str:
         s = s.replace(anchor, "      " + _clock("_pgs", k - 1, first=(k == 0)) + "\n" + anchor)
     # the overflow part ends with each sweep (the clamp rows' clock restarts
     # the next one), so its clock goes at the end of the sweep loop's body
-    end = "        sd[7] = lam[0]; sd[8] = lam[1]; sd[9] = lam[2];\n      }\n    }\n"
+    end = "        sd[8] = lam[0]; sd[9] = lam[1]; sd[10] = lam[2];\n      }\n    }\n"
     if s.count(end) != 1:
         raise RuntimeError("end of the projected Gauss-Seidel sweep not found")
     s = s.replace(end, end[:-len("    }\n")] + "      " + _clock("_pgs", 2) + "\n    }\n", 1)

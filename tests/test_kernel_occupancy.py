@@ -1,7 +1,7 @@
 """Waves per SIMD of the rollout kernels, from the compiler's resource report
 of the last build and the size of their LDS areas (160 KB per CU, four SIMDs):
 two waves for every plane and self-collision family of 20 DoFs and more with at
-most 8 contacts in registers, three or four for the smaller ones."""
+most 8 contacts in registers, three for the smaller ones."""
 import json
 import os
 import re
@@ -17,9 +17,7 @@ CU_LDS = 160 * 1024
 def _expected(nvc, ncr, ball, self_):
     if nvc > 16:
         return 1 if ncr > 8 or (ball and nvc > 24) else 2
-    if ncr > 8:
-        return 2
-    return 3 if ball or self_ or nvc <= 12 else 4
+    return 2 if ncr > 8 else 3
 
 
 def test_registers_and_lds_allow_the_waves_per_simd():
