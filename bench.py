@@ -209,11 +209,10 @@ def main():
         # (free fall, few contacts) rank the launch options differently
         options, trials = autotune(pop, T_pilot=T, log=lambda m: print(m, file=sys.stderr, flush=True))
     # per-bin launch timing (HIP events around each bin's launches) cannot be
-    # recorded inside a captured graph: a graph-replayed run is timed as is and
-    # the per-kernel figures come from one more rollout of the same layout
-    # launched eagerly
-    graph = bool(options.get("use_graph"))
-    sim = Simulator(pop, time_launches=not graph, **options)
+    # recorded inside a captured graph and takes bins that go out in one launch
+    # apart: the rollouts are timed as a program runs them, and the per-kernel
+    # figures come from one more rollout of the same layout
+    sim = Simulator(pop, **options)
     stream = torch.cuda.current_stream()
     for _ in range(args.warmup):
         sim.rollout(T)
@@ -240,19 +239,16 @@ def main():
         dst.copy_(src)
         torch.cuda.synchronize()
         del src, dst
-    if graph:
-        sim_t = Simulator(pop, time_launches=True, **dict(options, use_graph=False))
-        sim_t.rollout(T)
-        torch.cuda.synchronize()
-        times, vb, bins, facs = sim_t.launch_times(), sim_t.variant_bins(), sim_t.bins(), sim_t.bin_factorization()
-        sim_t.close()
-    else:
-        times, vb, bins, facs = sim.launch_times(), sim.variant_bins(), sim.bins(), sim.bin_factorization()
+    sim_t = Simulator(pop, time_launches=True, **dict(options, use_graph=False))
+    sim_t.rollout(T)
+    torch.cuda.synchronize()
+    times, vb, bins, facs = sim_t.launch_times(), sim_t.variant_bins(), sim_t.bins(), sim_t.bin_factorization()
+    sim_t.close()
     rows_contact, rows_clamp, status = sim.counters()
     fl_var = flops_per_variant(pop, T, rows_contact, rows_clamp,
                                factorization=np.array([facs[b] for b in vb]))
     fl = fl_var.sum()
-    # dominant kernel: the bin whose launches took longest in the last rollout
+    # dominant kernel: the bin whose launches took longest in that rollout
     # (HIP events around its launches on its own stream)
     dom = int(np.argmax([t[0] for t in times]))
     dom_ms, dom_launches = times[dom]

@@ -155,8 +155,10 @@ typedef struct {
  *  use_graph              != 0: sim_rollout replays a captured hipGraph
  *  steps_per_launch       simulation steps per kernel launch (0 = 1000)
  *  streams                concurrent streams the bins are spread over, by
- *                         longest-first assignment (0 = one per bin; 1 = the
- *                         caller's stream only)
+ *                         longest-first assignment (1 = the caller's stream
+ *                         only; 0 = chosen: several plane bins without
+ *                         time_launches go out in one launch per chunk of
+ *                         steps, otherwise one stream per bin)
  *  min_body_slots         0 or 16: smallest body capacity that holds each
  *                         variant; 32: every variant in 32-body kernels (fewer
  *                         bins)

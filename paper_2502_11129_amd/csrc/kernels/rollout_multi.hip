@@ -1,14 +1,18 @@
-// One launch for all bins of a population whose bins are all 32-body
-// kernels of the default contact budgets (the autotuned packing of the
-// uneven-morphology trees).  Each workgroup finds its bin from the block
-// ranges and runs that family's step loop; the LDS area is the largest
-// family's, shared by all.
+// One launch for all bins of a population: the plane families that the default
+// and the autotuned packings of uneven robots use.  Each workgroup finds its bin
+// from the block ranges and runs that family's step loop; the LDS area and the
+// register budget (256, two waves per SIMD) are the largest family's, shared by
+// all, so 2048 waves (8192 robots) are resident at once.  Bins on streams of
+// their own depend on how the runtime maps those to hardware queues; see
+// sim_create for the figures.
 #include "../rollout_kernel.hpp"
 #include "../launch.h"
 
 namespace simk {
 
-#define SIMK_MULTI_FAMILIES(X) X(16, 2, 8) X(16, 2, 16) X(20, 2, 8) X(24, 2, 8) X(28, 2, 8)
+#define SIMK_MULTI_FAMILIES(X)                                                                 \
+  X(8, 1, 8) X(12, 1, 8) X(16, 1, 8) X(16, 2, 8) X(16, 2, 16) X(20, 1, 4) X(20, 1, 8) X(20, 2, 8)  \
+  X(24, 1, 8) X(24, 2, 8) X(28, 2, 8)
 
 #define SIMK_MULTI_ENTRY(NVC, SB, NCR) {NVC, SB, NCR},
 const MultiFamily kMultiFamilies[] = {SIMK_MULTI_FAMILIES(SIMK_MULTI_ENTRY)};

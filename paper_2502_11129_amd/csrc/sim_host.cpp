@@ -27,6 +27,7 @@ namespace {
 constexpr int kNvCaps[] = {8, 12, 16, 20, 24, 28};
 constexpr int kMaxNv = 28;
 constexpr int kMaxBodiesPerVariant = 32;
+constexpr long long kSimds = 1024;       // SIMDs of an MI355X (256 CUs of four)
 constexpr int kStepsPerLaunch = 1000;  // default: long runs are split so each launch stays short
 
 std::string g_create_error;
@@ -505,18 +506,41 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
     return wave_cost(x) != wave_cost(y) ? wave_cost(x) > wave_cost(y) : cost(x) > cost(y);
   });
   // single launch: every bin must be one of the multi-bin kernel's families
+  auto find_multi = [&](Bin& b) {
+    for (int k = 0; k < kNumMultiFamilies; ++k)
+      if (kMultiFamilies[k].nvc == b.nvc && kMultiFamilies[k].sb == b.sb && kMultiFamilies[k].ncr == b.ncr)
+        b.multi_kind = k;
+    return b.multi_kind >= 0;
+  };
   if (hp->opts.single_launch) {
     if ((int)hp->bins.size() > kMaxMultiBins) return bad("single_launch supports at most 8 bins");
     if (ball || self) return bad("single_launch: the multi-bin kernel has no ball or self-collision families");
-    for (Bin& b : hp->bins) {
-      for (int k = 0; k < kNumMultiFamilies; ++k)
-        if (kMultiFamilies[k].nvc == b.nvc && kMultiFamilies[k].sb == b.sb && kMultiFamilies[k].ncr == b.ncr)
-          b.multi_kind = k;
-      if (b.multi_kind < 0)
+    for (Bin& b : hp->bins)
+      if (b.sb != 2 || !find_multi(b))
         return bad("single_launch: bin (nv capacity " + std::to_string(b.nvc) + ", " + std::to_string(16 * b.sb) +
                    " bodies, " + std::to_string(b.ncr) + " contacts in registers) is not in the multi-bin kernel");
-    }
     hp->multi = true;
+  } else if (hp->opts.streams == 0 && !hp->opts.time_launches && !ball && !self && hp->bins.size() > 1 &&
+             (int)hp->bins.size() <= kMaxMultiBins) {
+    // Neither streams nor per-bin launch times asked for: several plane bins go
+    // out in one launch.  On their own streams they depend on the process's
+    // four hardware queues: more bins than queues, or other handles' streams,
+    // put two bins in one queue, which then run after each other.  4096 / 8192 /
+    // 32768 random trees x 1000 steps take 33.5 / 36.7 / 109 ms in one launch and
+    // 57.3 / 59.7 / 111 ms on six streams; four merged bins on four streams match
+    // it (34.0 / 36.2 / 110 ms) until three handles take turns (36.7 against
+    // 54.2 ms).  Every workgroup then has the largest family's registers, two
+    // waves per SIMD: populations of small robots alone that need more of them
+    // (three fit) keep their own launches.
+    long long waves = 0;
+    bool covered = true, large = false, tree = false;
+    for (Bin& b : hp->bins) {
+      waves += ((long long)b.users.size() + kVarPerWave - 1) / kVarPerWave;
+      covered = find_multi(b) && covered;
+      large = large || b.nvc > 16;
+      tree = tree || b.tree;
+    }
+    hp->multi = covered && !tree && (large || waves <= 2 * kSimds);
   }
   // streams: longest-first assignment of the bins to the least-loaded stream
   {
