@@ -236,16 +236,9 @@ int sur_predict(sur_handle* h, int64_t n, const uint16_t* X, int64_t x_rows, con
   if (!idx && x_rows < n) return fail(h, SUR_E_INVALID, "x_rows < n without idx");
   hipStream_t s = (hipStream_t)stream;
   const Work& w = h->w;
-  for (int64_t r0 = 0; r0 < n; r0 += h->rows) {
-    const int rows = (int)((n - r0) < h->rows ? (n - r0) : h->rows);
-    // without idx, the chunk's rows start at X + r0 rows
-    const uint16_t* Xc = idx ? X : X + r0 * kFeat;
-    const int32_t* ic = idx ? idx + r0 : nullptr;
-    rc = forward_rows(h, rows, Xc, x_rows, ic, false, s);
-    if (rc) return rc;
-    SUR_HIP(h, head(rows, w.h3, w.w4f, w.p + kOffB4, y + r0, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, s),
-            "head");
-  }
+  SUR_HIP(h, predict(n, X, x_rows, idx, w.wt1, w.wt2, w.wt3, w.p + kOffB1, w.p + kOffB2, w.p + kOffB3, w.w4f,
+                     w.p + kOffB4, y, s),
+          "predict");
   return SUR_OK;
 }
 

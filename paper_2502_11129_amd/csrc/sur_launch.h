@@ -55,6 +55,12 @@ struct GemmArgs {
 
 hipError_t gemm(int alayout, int blayout, int epi, const GemmArgs& a, hipStream_t s);
 
+// Predictions of n rows of X (x_rows stored rows; idx: optional gather, an index
+// outside gives NaN) in one launch: y = head(GELU layers), weights wt_l[out][in].
+hipError_t predict(int64_t n, const uint16_t* X, int64_t x_rows, const int32_t* idx, const uint16_t* wt1,
+                   const uint16_t* wt2, const uint16_t* wt3, const float* b1, const float* b2, const float* b3,
+                   const float* w4, const float* b4, float* y, hipStream_t s);
+
 hipError_t features(int64_t n, const int32_t* nh, const int8_t* parent, const int8_t* face, const int8_t* axis,
                     const float* cpg, uint16_t* X, hipStream_t s);
 
