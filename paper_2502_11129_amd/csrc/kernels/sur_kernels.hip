@@ -30,177 +30,9 @@ __device__ inline uint16_t f2bf(float f) {
 __device__ inline float bf2f(uint32_t b) { return __uint_as_float((b & 0xffffu) << 16); }
 
 __device__ inline float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ inline float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
-}
 
-// ----------------------------------------------------------------------------- GEMM
-constexpr int BM = 64, BN = 64, BK = 32;
-constexpr int LS = BK + 8;  // LDS row stride in BF16 elements (80 bytes: keeps 16-byte alignment)
 constexpr uint16_t kOne = 0x3F80;
 constexpr uint16_t kNaN = 0x7FC0;
-
-// Stage the logical 64 x 32 tile (rows r0.., k0..) of an operand into S[row][k].
-// kRowK: element (r, k) at P[srow(r) * ld + k]; kRowM: at P[srow(k) * ld + r].
-// Rows >= R and k >= K read as zero; logical row onesRow reads as one and the
-// rows after it as zero (its stored width is onesRow, a multiple of 8).  A
-// gathered stored row outside [0, rows) reads as NaN.
-template <int L>
-__device__ inline void load_tile(uint16_t* S, const uint16_t* __restrict__ P, int ld, const int32_t* __restrict__ gather,
-                                 int64_t rows, int onesRow, int R, int K, int r0, int k0, int t) {
-  if (L == kRowK) {
-    const int r = t >> 2, c = (t & 3) * 8, gr = r0 + r, gk = k0 + c;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (gr < R && gk < K) {
-      if (onesRow >= 0 && gr >= onesRow) {
-        if (gr == onesRow) {
-          uint16_t e[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) e[j] = (gk + j < K) ? kOne : 0;
-          v = *reinterpret_cast<uint4*>(e);
-        }
-      } else {
-        const int64_t srow = gather ? gather[gr] : gr;
-        const uint16_t* p = P + srow * ld + gk;
-        if (gather && (srow < 0 || srow >= rows)) {
-          uint16_t e[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) e[j] = (gk + j < K) ? kNaN : 0;
-          v = *reinterpret_cast<uint4*>(e);
-        } else if (gk + 8 <= K) {
-          v = *reinterpret_cast<const uint4*>(p);
-        } else {
-          uint16_t e[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) e[j] = (gk + j < K) ? p[j] : 0;
-          v = *reinterpret_cast<uint4*>(e);
-        }
-      }
-    }
-    *reinterpret_cast<uint4*>(&S[r * LS + c]) = v;
-  } else {
-    const int kk = t >> 3, c = (t & 7) * 8, gk = k0 + kk, gr = r0 + c;
-    uint16_t e[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) e[j] = 0;
-    if (gk < K && gr < R) {
-      if (onesRow >= 0 && gr >= onesRow) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = (gr + j == onesRow) ? kOne : 0;
-      } else {
-        const int64_t srow = gather ? gather[gk] : gk;
-        const uint16_t* p = P + srow * ld + gr;
-        if (gather && (srow < 0 || srow >= rows)) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) e[j] = (gr + j < R) ? kNaN : 0;
-        } else if (gr + 8 <= R) {
-          *reinterpret_cast<uint4*>(e) = *reinterpret_cast<const uint4*>(p);
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) e[j] = (gr + j < R) ? p[j] : 0;
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) S[(c + j) * LS + kk] = e[j];
-  }
-}
-
-template <int AL, int BL, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[BM * LS];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LS];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // K range of this layer (the whole of K unless the product is split)
-  const int kchunk = a.ksplit > 1 ? ((a.K + a.ksplit - 1) / a.ksplit + BK - 1) / BK * BK : a.K;
-  const int kbeg = blockIdx.z * kchunk;
-  const int kend = min(a.K, kbeg + kchunk);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    load_tile<AL>(As, a.A, a.lda, a.gatherA, a.rowsA, a.onesRow, a.M, a.K, m0, k0, t);
-    load_tile<BL>(Bs, a.B, a.ldb, nullptr, 0, -1, a.N, a.K, n0, k0, t);
-    __syncthreads();
-    bf16x8 af[2], bfr[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint4 ua = *reinterpret_cast<const uint4*>(&As[(wm + i * 16 + (lane & 15)) * LS + 8 * (lane >> 4)]);
-      const uint4 ub = *reinterpret_cast<const uint4*>(&Bs[(wn + i * 16 + (lane & 15)) * LS + 8 * (lane >> 4)]);
-      af[i] = __builtin_bit_cast(bf16x8, ua);
-      bfr[i] = __builtin_bit_cast(bf16x8, ub);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + j * 16 + (lane & 15);
-        if (m >= a.M || n >= a.N) continue;
-        const float v = acc[i][j][r];
-        const int64_t o = (int64_t)m * a.ldc + n;
-        if (EPI == kEpiGelu) {
-          const float z = v + a.bias[n];
-          if (a.zout) a.zout[o] = z;
-          a.hout[o] = f2bf(gelu(z));
-        } else if (EPI == kEpiGeluGrad) {
-          const float z = a.zin[(int64_t)m * a.ldz + n];
-          a.hout[o] = f2bf(v * gelu_grad(z));
-        } else if (a.ksplit > 1) {
-          a.partial[(size_t)blockIdx.z * a.M * a.N + (size_t)m * a.N + n] = v;
-        } else {
-          a.fout[o] = v;
-        }
-      }
-}
-
-// Sum of the split-K layers in layer order (deterministic): out[m][n] = sum_z partial[z][m][n].
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int layers, const float* __restrict__ partial,
-                                                            float* __restrict__ out, int ldc) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)M * N) return;
-  float s = 0.f;
-  for (int z = 0; z < layers; ++z) s += partial[(size_t)z * M * N + i];
-  const int m = (int)(i / N), n = (int)(i % N);
-  out[(int64_t)m * ldc + n] = s;
-}
-
-template <int AL, int BL, int EPI>
-static hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
-  const int layers = (EPI == kEpiF32 && a.ksplit > 1) ? a.ksplit : 1;
-  dim3 grid((a.N + BN - 1) / BN, (a.M + BM - 1) / BM, layers);
-  hipLaunchKernelGGL((gemm_kernel<AL, BL, EPI>), grid, dim3(256), 0, s, a);
-  if (layers > 1) {
-    const int64_t total = (int64_t)a.M * a.N;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a.M, a.N, layers,
-                       a.partial, a.fout, a.ldc);
-  }
-  return hipGetLastError();
-}
-
-hipError_t gemm(int al, int bl, int epi, const GemmArgs& a, hipStream_t s) {
-  if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  // the combinations the surrogate uses
-  if (al == kRowK && bl == kRowK && epi == kEpiGelu) return launch_gemm<kRowK, kRowK, kEpiGelu>(a, s);
-  if (al == kRowK && bl == kRowK && epi == kEpiGeluGrad) return launch_gemm<kRowK, kRowK, kEpiGeluGrad>(a, s);
-  if (al == kRowM && bl == kRowM && epi == kEpiF32) return launch_gemm<kRowM, kRowM, kEpiF32>(a, s);
-  if (al == kRowK && bl == kRowK && epi == kEpiF32) return launch_gemm<kRowK, kRowK, kEpiF32>(a, s);
-  return hipErrorInvalidValue;
-}
 
 // ----------------------------------------------------------------------------- whole-network prediction
 // The four layers of one tile of 16 NT rows without leaving the CU.  A
@@ -208,8 +40,7 @@ hipError_t gemm(int al, int bl, int epi, const GemmArgs& a, hipStream_t s) {
 // their registers, 32 output columns each (160 registers), and walk over tiles;
 // activations go from layer to layer through LDS in BF16.  The products run
 // with the weights as the row operand, so a lane's four results are four
-// consecutive columns of one row and go to LDS as eight bytes.  k ascends as in
-// gemm_kernel and the head sums as head_kernel does: the same values bit for bit.
+// consecutive columns of one row and go to LDS as eight bytes.
 // 1 M rows: 600 us, 550 TFLOP/s; layer at a time, with the activations (1.5 KB a
 // row) through HBM, 1816 us.  10 007 rows: 17 us, 39 in four launches.  What bounds
 // it is the exact erf of 768 GELUs a row (20 to 46 VALU instructions each, by the
@@ -217,13 +48,13 @@ hipError_t gemm(int al, int bl, int epi, const GemmArgs& a, hipStream_t s) {
 constexpr int kPredWaves = 8;
 constexpr int kXS = kFeat + 8, kHS = kHid + 8;  // LDS row strides in BF16 (16-byte aligned, banks spread)
 
-// Sum over the 64 lanes in the order of wave_sum (lane distances 32, 16, 8, 4,
-// 2, 1) without going through LDS; every lane gets the result.
+// Sum over the 64 lanes by lane distances 32, 16, 8, 4, 2, 1, without LDS; every
+// lane gets the result.
 template <int CTRL>
 __device__ inline float dpp_move(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-__device__ inline float wave_sum_dpp(float v) {
+__device__ inline float wave_sum(float v) {
   auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
   a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -367,7 +198,7 @@ void predict_kernel(int64_t n, const uint16_t* __restrict__ X, int64_t x_rows, c
     for (int q = 0; q < R / kPredWaves; ++q) {
       const int r = wave + q * kPredWaves;
       const uint2 hv = *reinterpret_cast<const uint2*>(&ha[r * kHS + 4 * lane]);
-      const float v = wave_sum_dpp(bf2f(hv.x) * wv.x + bf2f(hv.x >> 16) * wv.y + bf2f(hv.y) * wv.z +
+      const float v = wave_sum(bf2f(hv.x) * wv.x + bf2f(hv.x >> 16) * wv.y + bf2f(hv.y) * wv.z +
                                    bf2f(hv.y >> 16) * wv.w);
       const int64_t row = tile * R + r;
       if (lane == 0 && row < n) y[row] = v + b4v;
@@ -499,94 +330,6 @@ hipError_t features(int64_t n, const int32_t* nh, const int8_t* parent, const in
   return hipGetLastError();
 }
 
-// ----------------------------------------------------------------------------- head
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// One wave per row; lane l owns hidden units 4l .. 4l+3.
-__global__ __launch_bounds__(256) void head_kernel(int n, const uint16_t* __restrict__ h3, const float* __restrict__ w4,
-                                                   const float* __restrict__ b4, float* __restrict__ y_out,
-                                                   const float* __restrict__ target, const int32_t* __restrict__ idx,
-                                                   int64_t rows, const float* __restrict__ z3, float* __restrict__ r,
-                                                   float* __restrict__ dy, uint16_t* __restrict__ dz3) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= n) return;
-  const uint2 hv = *reinterpret_cast<const uint2*>(h3 + (int64_t)row * kHid + 4 * lane);
-  const float4 wv = *reinterpret_cast<const float4*>(w4 + 4 * lane);
-  float s = bf2f(hv.x) * wv.x + bf2f(hv.x >> 16) * wv.y + bf2f(hv.y) * wv.z + bf2f(hv.y >> 16) * wv.w;
-  s = wave_sum(s);
-  const float y = s + b4[0];
-  if (target == nullptr) {
-    if (lane == 0) y_out[row] = y;
-    return;
-  }
-  const int64_t ti = idx ? (int64_t)idx[row] : (int64_t)row;
-  const float rr = (ti >= 0 && ti < rows) ? y - target[ti] : __builtin_nanf("");
-  const float d = 2.0f * rr / (float)n;
-  if (lane == 0) {
-    y_out[row] = y;
-    r[row] = rr;
-    dy[row] = d;
-  }
-  const float4 zv = *reinterpret_cast<const float4*>(z3 + (int64_t)row * kHid + 4 * lane);
-  const uint32_t o0 = f2bf(d * wv.x * gelu_grad(zv.x)) | ((uint32_t)f2bf(d * wv.y * gelu_grad(zv.y)) << 16);
-  const uint32_t o1 = f2bf(d * wv.z * gelu_grad(zv.z)) | ((uint32_t)f2bf(d * wv.w * gelu_grad(zv.w)) << 16);
-  *reinterpret_cast<uint2*>(dz3 + (int64_t)row * kHid + 4 * lane) = make_uint2(o0, o1);
-}
-
-hipError_t head(int n, const uint16_t* h3, const float* w4, const float* b4, float* y_out, const float* target,
-                const int32_t* idx, int64_t rows, const float* z3, float* r, float* dy, uint16_t* dz3, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(head_kernel, dim3((n + 3) / 4), dim3(256), 0, s, n, h3, w4, b4, y_out, target, idx, rows, z3, r,
-                     dy, dz3);
-  return hipGetLastError();
-}
-
-// Column c < 256: sum_m h3[m][c] dy[m]; c = 256: sum dy; c = 257: sum r^2.
-constexpr int kHeadCols = kHid + 2;
-
-__global__ __launch_bounds__(320) void head_partial_kernel(int n, const uint16_t* __restrict__ h3,
-                                                           const float* __restrict__ dy, const float* __restrict__ r,
-                                                           float* __restrict__ partial) {
-  const int c = threadIdx.x;
-  if (c >= kHeadCols) return;
-  const int r0 = blockIdx.x * kHeadChunk;
-  const int r1 = min(n, r0 + kHeadChunk);
-  float s = 0.f;
-  if (c < kHid) {
-    for (int m = r0; m < r1; ++m) s += bf2f(h3[(int64_t)m * kHid + c]) * dy[m];
-  } else if (c == kHid) {
-    for (int m = r0; m < r1; ++m) s += dy[m];
-  } else {
-    for (int m = r0; m < r1; ++m) s += r[m] * r[m];
-  }
-  partial[blockIdx.x * kHeadCols + c] = s;
-}
-
-__global__ __launch_bounds__(320) void head_final_kernel(int n, int chunks, const float* __restrict__ partial,
-                                                         float* __restrict__ gW4, float* __restrict__ gb4,
-                                                         float* __restrict__ loss) {
-  const int c = threadIdx.x;
-  if (c >= kHeadCols) return;
-  float s = 0.f;
-  for (int q = 0; q < chunks; ++q) s += partial[q * kHeadCols + c];
-  if (c < kHid) gW4[c] = s;
-  else if (c == kHid) gb4[0] = s;
-  else if (loss) loss[0] = s / (float)n;
-}
-
-hipError_t head_reduce(int n, const uint16_t* h3, const float* dy, const float* r, float* partial, float* gW4,
-                       float* gb4, float* loss, hipStream_t s) {
-  const int chunks = (n + kHeadChunk - 1) / kHeadChunk;
-  hipLaunchKernelGGL(head_partial_kernel, dim3(chunks), dim3(320), 0, s, n, h3, dy, r, partial);
-  hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(320), 0, s, n, chunks, partial, gW4, gb4, loss);
-  return hipGetLastError();
-}
-
 // ----------------------------------------------------------------------------- Adam + BF16 copies
 struct Copies {
   uint16_t *wt1, *wt2, *wt3, *wb2, *wb3;
@@ -612,20 +355,30 @@ __device__ inline void write_copy(int i, float val, const Copies& c) {
   }
 }
 
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                                                   const float* __restrict__ g, float c1, float c2, float lr, float b1,
-                                                   float omb1, float b2, float omb2, float eps, Copies cp) {
+struct AdamArgs {
+  float *p, *m, *v;
+  float c1, c2, lr, b1, omb1, b2, omb2, eps;
+};
+// 1 - beta and the bias corrections 1 - beta^t are formed in double, then rounded once
+static AdamArgs adam_args(float* p, float* m, float* v, int64_t t, double lr, double b1, double b2, double eps) {
+  return AdamArgs{p, m, v, (float)(1.0 - pow(b1, (double)t)), (float)(1.0 - pow(b2, (double)t)), (float)lr,
+                  (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps};
+}
+__device__ inline void adam_update(int i, float gi, const AdamArgs& a, const Copies& cp) {
+  const float mi = a.b1 * a.m[i] + a.omb1 * gi;
+  const float vi = a.b2 * a.v[i] + a.omb2 * gi * gi;
+  const float mh = mi / a.c1, vh = vi / a.c2;
+  const float pi = a.p[i] - a.lr * mh / (sqrtf(vh) + a.eps);
+  a.m[i] = mi;
+  a.v[i] = vi;
+  a.p[i] = pi;
+  write_copy(i, pi, cp);
+}
+
+__global__ __launch_bounds__(256) void adam_kernel(const float* __restrict__ g, AdamArgs a, Copies cp) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= kNParams) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + omb1 * gi;
-  const float vi = b2 * v[i] + omb2 * gi * gi;
-  const float mh = mi / c1, vh = vi / c2;
-  const float pi = p[i] - lr * mh / (sqrtf(vh) + eps);
-  m[i] = mi;
-  v[i] = vi;
-  p[i] = pi;
-  write_copy(i, pi, cp);
+  adam_update(i, g[i], a, cp);
 }
 
 __global__ __launch_bounds__(256) void refresh_kernel(const float* __restrict__ p, Copies cp) {
@@ -637,12 +390,8 @@ __global__ __launch_bounds__(256) void refresh_kernel(const float* __restrict__ 
 hipError_t adam(float* p, float* m, float* v, const float* g, int64_t t, double lr, double b1, double b2, double eps,
                 uint16_t* wt1, uint16_t* wt2, uint16_t* wt3, uint16_t* wb2, uint16_t* wb3, float* w4f,
                 hipStream_t s) {
-  // 1 - beta and the bias corrections 1 - beta^t are formed in double, then rounded once
-  const float c1 = (float)(1.0 - pow(b1, (double)t));
-  const float c2 = (float)(1.0 - pow(b2, (double)t));
-  Copies cp{wt1, wt2, wt3, wb2, wb3, w4f};
-  hipLaunchKernelGGL(adam_kernel, dim3((kNParams + 255) / 256), dim3(256), 0, s, p, m, v, g, c1, c2, (float)lr,
-                     (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps, cp);
+  hipLaunchKernelGGL(adam_kernel, dim3((kNParams + 255) / 256), dim3(256), 0, s, g,
+                     adam_args(p, m, v, t, lr, b1, b2, eps), Copies{wt1, wt2, wt3, wb2, wb3, w4f});
   return hipGetLastError();
 }
 
@@ -650,6 +399,329 @@ hipError_t refresh_copies(const float* p, uint16_t* wt1, uint16_t* wt2, uint16_t
                           uint16_t* wb3, float* w4f, hipStream_t s) {
   Copies cp{wt1, wt2, wt3, wb2, wb3, w4f};
   hipLaunchKernelGGL(refresh_kernel, dim3((kNParams + 255) / 256), dim3(256), 0, s, p, cp);
+  return hipGetLastError();
+}
+
+// ----------------------------------------------------------------------------- training step
+// A step is three launches: activations and their gradients of all rows, the
+// weight-gradient products, the parameter update.  (Layer at a time it was
+// thirteen, 175 us a batch of 4096, most of it launches and single-block sums.)
+//
+// Activations, features and gradients that the weight products read are kept
+// in BF16 blocks of 16 rows, transposed: element (row, col) of a matrix of W
+// columns at ((row / 16) W + col) 16 + row % 16.  The products sum over rows, so
+// this is the order in which a lane wants its eight operands, and both sides
+// move whole lines.
+__device__ inline int64_t blk16(int64_t row, int col, int width) {
+  return ((row >> 4) * width + col) * 16 + (row & 15);
+}
+
+// GELU and its derivative from one erf.
+__device__ inline void gelu_pair(float z, float* h, float* d) {
+  const float e1 = 1.0f + erff(z * 0.70710678118654752f);
+  *h = 0.5f * z * e1;
+  *d = 0.5f * e1 + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+}
+
+// An LDS tile of R rows (stride ST) to its transposed blocks at row0.
+template <int R, int ST, int W>
+__device__ inline void store_blocks(const uint16_t* tile, uint16_t* __restrict__ out, int64_t row0, int tid) {
+  for (int e = tid; e < W * (R / 8); e += 64 * kPredWaves) {
+    const int c = e % W, r = (e / W) * 8;
+    uint32_t v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      v[j] = (uint32_t)tile[(r + 2 * j) * ST + c] | ((uint32_t)tile[(r + 2 * j + 1) * ST + c] << 16);
+    *reinterpret_cast<uint4*>(out + blk16(row0 + r, c, W)) = make_uint4(v[0], v[1], v[2], v[3]);
+  }
+}
+
+// Forward and backward over the layers for one tile of 16 batch rows per
+// workgroup, as in predict_kernel, the weights of two layers in registers at a
+// time; z never leaves the registers (GELU' is formed with GELU), the gradients
+// take the way back through the same LDS buffers.  Rows past the batch have zero
+// features and zero gradient.  Bound by the weights' way from L2 (590 KB a
+// workgroup) and the erf and exp of 768 units a row.  Six batches of 4096 (a
+// launch per layer and direction before, activations through HBM): 1053 -> 243 us
+// in the three launches, a batch 25 us here, 10 us in the weight gradients and
+// 6 us in the update.
+__global__ __launch_bounds__(64 * kPredWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void train_rows_kernel(TrainArgs a) {
+  constexpr int NT = 1, R = 16 * NT;
+  constexpr int T = 64 * kPredWaves;
+  __shared__ __attribute__((aligned(16))) uint16_t xs[R * kXS];
+  __shared__ __attribute__((aligned(16))) uint16_t hs[2][R * kHS];
+  __shared__ __attribute__((aligned(16))) float bias[3][kHid];
+  __shared__ __attribute__((aligned(16))) float w4s[kHid];
+  __shared__ float dys[R], ts[R];  // dL/dy and target of each row
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
+  const int c0 = 32 * wave;
+  const int64_t row0 = (int64_t)blockIdx.x * R;
+
+  for (int e = tid; e < R * (kFeat / 8); e += T) {
+    const int r = e >> 4, c = e & 15;
+    const int64_t row = row0 + r;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row < a.B) {
+      const int64_t src = a.idx[row];
+      if (src >= 0 && src < a.x_rows) v = *reinterpret_cast<const uint4*>(a.X + src * kFeat + c * 8);
+      else v = make_uint4(kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u);
+    }
+    *reinterpret_cast<uint4*>(&xs[r * kXS + c * 8]) = v;
+  }
+  // the targets now: in the head their two dependent loads would stop every wave
+  if (tid >= T - R && row0 + tid - (T - R) < a.B) {
+    const int64_t ti = a.idx[row0 + tid - (T - R)];
+    ts[tid - (T - R)] = (ti >= 0 && ti < a.x_rows) ? a.target[ti] : __builtin_nanf("");
+  }
+  for (int e = tid; e < kHid; e += T) {
+    bias[0][e] = a.p[kOffB1 + e];
+    bias[1][e] = a.p[kOffB2 + e];
+    bias[2][e] = a.p[kOffB3 + e];
+    w4s[e] = a.w4[e];
+  }
+  bf16x8 wa[2][kHid / 32], wb[2][kHid / 32], w1[2][kFeat / 32];
+  load_weights(w1, a.wt1, c0, r16, g);
+  load_weights(wa, a.wt2, c0, r16, g);
+  const float b4 = a.p[kOffB4];
+  __syncthreads();
+
+  f32x4 acc[2][NT], d1[2][NT], d2[2][NT], d3[2][NT];
+  // h = bf16(GELU(acc + b)) to LDS, GELU' to d
+  auto activate = [&](const float* b, uint16_t* h, f32x4 (&d)[2][NT]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const float4 bv = *reinterpret_cast<const float4*>(&b[c0 + m * 16 + 4 * g]);
+      const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        float hv[4], dv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          gelu_pair(acc[m][t][i] + bb[i], &hv[i], &dv[i]);
+          d[m][t][i] = dv[i];
+        }
+        *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) =
+            make_uint2(pack_bf16(hv[0], hv[1]), pack_bf16(hv[2], hv[3]));
+      }
+    }
+  };
+  // dz = bf16(v * GELU') to LDS
+  auto put_grad = [&](const f32x4 (&v)[2][NT], const f32x4 (&d)[2][NT], uint16_t* h) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) =
+            make_uint2(pack_bf16(v[m][t][0] * d[m][t][0], v[m][t][1] * d[m][t][1]),
+                       pack_bf16(v[m][t][2] * d[m][t][2], v[m][t][3] * d[m][t][3]));
+  };
+
+  store_blocks<R, kXS, kFeat>(xs, a.XT, row0, tid);
+  tile_product<kFeat / 32, kXS, NT>(w1, xs, r16, g, acc);
+  load_weights(wb, a.wt3, c0, r16, g);
+  activate(bias[0], hs[0], d1);
+  __syncthreads();
+  store_blocks<R, kHS, kHid>(hs[0], a.h1T, row0, tid);
+  tile_product<kHid / 32, kHS, NT>(wa, hs[0], r16, g, acc);
+  load_weights(wa, a.wb3, c0, r16, g);
+  activate(bias[1], hs[1], d2);
+  __syncthreads();
+  store_blocks<R, kHS, kHid>(hs[1], a.h2T, row0, tid);
+  tile_product<kHid / 32, kHS, NT>(wb, hs[1], r16, g, acc);
+  load_weights(wb, a.wb2, c0, r16, g);
+  activate(bias[2], hs[0], d3);
+  __syncthreads();
+  // head: one wave per row, lane l owns hidden units 4l .. 4l+3
+  {
+    const float4 wv = *reinterpret_cast<const float4*>(&w4s[4 * lane]);
+#pragma unroll
+    for (int q = 0; q < R / kPredWaves; ++q) {
+      const int r = wave + q * kPredWaves;
+      const int64_t row = row0 + r;
+      const uint2 hv = *reinterpret_cast<const uint2*>(&hs[0][r * kHS + 4 * lane]);
+      const float s = wave_sum(bf2f(hv.x) * wv.x + bf2f(hv.x >> 16) * wv.y + bf2f(hv.y) * wv.z +
+                               bf2f(hv.y >> 16) * wv.w);
+      if (lane == 0) {
+        float rr = 0.f, d = 0.f;
+        if (row < a.B) {
+          rr = (s + b4) - ts[r];
+          d = 2.0f * rr / (float)a.B;
+          a.r[row] = rr;
+          a.dy[row] = d;
+        }
+        dys[r] = d;
+      }
+    }
+  }
+  store_blocks<R, kHS, kHid>(hs[0], a.h3T, row0, tid);
+  __syncthreads();
+  {
+    f32x4 v[2][NT];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const float4 wv = *reinterpret_cast<const float4*>(&w4s[c0 + m * 16 + 4 * g]);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float d = dys[t * 16 + r16];
+        v[m][t] = f32x4{d * wv.x, d * wv.y, d * wv.z, d * wv.w};
+      }
+    }
+    put_grad(v, d3, hs[1]);
+  }
+  __syncthreads();
+  store_blocks<R, kHS, kHid>(hs[1], a.d3T, row0, tid);
+  tile_product<kHid / 32, kHS, NT>(wa, hs[1], r16, g, acc);
+  put_grad(acc, d2, hs[0]);
+  __syncthreads();
+  store_blocks<R, kHS, kHid>(hs[0], a.d2T, row0, tid);
+  tile_product<kHid / 32, kHS, NT>(wb, hs[0], r16, g, acc);
+  put_grad(acc, d1, hs[1]);
+  __syncthreads();
+  store_blocks<R, kHS, kHid>(hs[1], a.d1T, row0, tid);
+}
+
+// Weight gradients [W_l; b_l] = [h | 1]^T dz_l over layer z of the batch rows (a
+// ones row of the activation operand gives the bias gradient), 128 x 128 outputs
+// per workgroup, 64 x 64 per wave straight from the transposed blocks, the
+// partial sums of each layer of rows in the flat parameter layout; in the last
+// workgroups the head's sums (W4, b4 and the squared residuals) over chunks of
+// kHeadChunk rows, each in row order.
+constexpr int kHeadCols = kHid + 2;
+constexpr int kGradTiles = 4 + 4 + 2;  // workgroups per layer of rows: W3, W2 (256 x 256), W1 (128 x 256)
+
+__global__ __launch_bounds__(256) void train_grad_kernel(TrainArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
+  if ((int)blockIdx.x >= kGradTiles * a.layers) {
+    // column c < 256: sum_m h3[m][c] dy[m]; c = 256: sum dy; c = 257: sum r^2
+    __shared__ float dys[kHeadChunk], rs[kHeadChunk];
+    const int q = blockIdx.x - kGradTiles * a.layers;
+    const int m0 = q * kHeadChunk, rows = min(a.B - m0, kHeadChunk);
+    if (tid < kHeadChunk) {
+      dys[tid] = tid < rows ? a.dy[m0 + tid] : 0.f;
+      rs[tid] = tid < rows ? a.r[m0 + tid] : 0.f;
+    }
+    __syncthreads();
+    // 64 rows in flight: one block at a time waits on memory once per 16 rows
+    float s = 0.f;
+    const int last = (rows - 1) / 16 * 16;
+    for (int m = 0; m < rows; m += 64) {
+      uint4 hb[8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint4* hp = reinterpret_cast<const uint4*>(a.h3T + blk16(m0 + min(m + 16 * u, last), tid, kHid));
+        hb[2 * u] = hp[0];
+        hb[2 * u + 1] = hp[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 64; ++j) {
+        const uint4 hv = hb[j >> 3];
+        const uint32_t hw = (j & 7) < 2 ? hv.x : (j & 7) < 4 ? hv.y : (j & 7) < 6 ? hv.z : hv.w;
+        const float next = s + bf2f(hw >> (16 * (j & 1))) * dys[m + j];
+        s = m + j < rows ? next : s;
+      }
+    }
+    a.head_partial[q * kHeadCols + tid] = s;
+    if (tid == 0) {  // the zeros past the last row change nothing
+      float t = 0.f;
+#pragma unroll 32
+      for (int m = 0; m < kHeadChunk; ++m) t += dys[m];
+      a.head_partial[q * kHeadCols + kHid] = t;
+    } else if (tid == 64) {
+      float t = 0.f;
+#pragma unroll 32
+      for (int m = 0; m < kHeadChunk; ++m) t += rs[m] * rs[m];
+      a.head_partial[q * kHeadCols + kHid + 1] = t;
+    }
+    return;
+  }
+  const int z = blockIdx.x / kGradTiles, tile = blockIdx.x % kGradTiles;
+  const int prod = tile < 4 ? 2 : tile < 8 ? 1 : 0;  // layer index: W3, W2, W1
+  const int tt = tile - (prod == 2 ? 0 : prod == 1 ? 4 : 8);
+  const int width = prod == 0 ? kFeat : kHid;        // columns of the activation operand
+  const uint16_t* h = prod == 2 ? a.h2T : prod == 1 ? a.h1T : a.XT;
+  const uint16_t* d = prod == 2 ? a.d3T : prod == 1 ? a.d2T : a.d1T;
+  const int mb = tt >> 1;
+  const int m0 = mb * 128 + (wave >> 1) * 64, n0 = (tt & 1) * 128 + (wave & 1) * 64;
+  const bool bias_row = mb == 0 && wave < 2;
+  f32x4 acc[4][4], accb[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const uint32_t one2 = r16 == 0 ? kOne * 0x10001u : 0u;
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(one2, one2, one2, one2));
+  const int kbeg = z * a.kchunk, kend = min(a.B, kbeg + a.kchunk);
+#pragma unroll 2
+  for (int k0 = kbeg; k0 < kend; k0 += 32) {
+    // rows past the batch up to the next multiple of 32 hold zero gradients
+    const int64_t row = k0 + 8 * g;
+    bf16x8 df[4], hf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      df[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(d + blk16(row, n0 + i * 16 + r16, kHid)));
+      hf[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(h + blk16(row, m0 + i * 16 + r16, width)));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], hf[j], acc[i][j], 0, 0, 0);
+      if (bias_row) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], ones, accb[i], 0, 0, 0);
+    }
+  }
+  float* out = a.partial + (size_t)z * kOffW4 + (prod == 2 ? kOffW3 : prod == 1 ? kOffW2 : kOffW1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<f32x4*>(&out[(m0 + j * 16 + r16) * kHid + n0 + i * 16 + 4 * g]) = acc[i][j];
+    if (bias_row && r16 == 0) *reinterpret_cast<f32x4*>(&out[width * kHid + n0 + i * 16 + 4 * g]) = accb[i];
+  }
+}
+
+// Gradient of every parameter (the layers' partial sums in layer order, the
+// head's in chunk order), Adam, and the BF16 copies of the new weights.
+__global__ __launch_bounds__(256) void train_update_kernel(TrainArgs a, AdamArgs ad, Copies cp) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i > kNParams) return;
+  float gi = 0.f;
+  if (i < kOffW4) {
+    float v[kMaxSplitK];
+#pragma unroll
+    for (int z = 0; z < kMaxSplitK; ++z) v[z] = z < a.layers ? a.partial[(size_t)z * kOffW4 + i] : 0.f;
+#pragma unroll
+    for (int z = 0; z < kMaxSplitK; ++z)
+      if (z < a.layers) gi += v[z];
+  } else {
+    const float* hp = a.head_partial + (i - kOffW4);
+#pragma unroll 8
+    for (int q = 0; q < a.chunks; ++q) gi += hp[q * kHeadCols];
+    if (i == kNParams) {
+      a.loss[0] = gi / (float)a.B;
+      return;
+    }
+  }
+  a.g[i] = gi;
+  adam_update(i, gi, ad, cp);
+}
+
+hipError_t train(const TrainArgs& args, float* p, float* m, float* v, int64_t t, double lr, double b1, double b2,
+                 double eps, uint16_t* wt1, uint16_t* wt2, uint16_t* wt3, uint16_t* wb2, uint16_t* wb3, float* w4f,
+                 hipStream_t s) {
+  TrainArgs a = args;
+  // the batch (the reduction) is long and a product's output small: split it over
+  // layers of at least kSplitKRows rows
+  a.layers = a.B / kSplitKRows < 1 ? 1 : a.B / kSplitKRows > kMaxSplitK ? kMaxSplitK : a.B / kSplitKRows;
+  a.kchunk = ((a.B + a.layers - 1) / a.layers + 31) / 32 * 32;
+  a.chunks = (a.B + kHeadChunk - 1) / kHeadChunk;
+  // whole 32-row steps of the products are written
+  const int rows = (a.B + 31) / 32 * 32;
+  hipLaunchKernelGGL(train_rows_kernel, dim3(rows / 16), dim3(64 * kPredWaves), 0, s, a);
+  hipLaunchKernelGGL(train_grad_kernel, dim3(kGradTiles * a.layers + a.chunks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(train_update_kernel, dim3(kNParams / 256 + 1), dim3(256), 0, s, a,
+                     adam_args(p, m, v, t, lr, b1, b2, eps), Copies{wt1, wt2, wt3, wb2, wb3, w4f});
   return hipGetLastError();
 }
 

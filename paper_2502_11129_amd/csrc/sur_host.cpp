@@ -16,20 +16,15 @@ using namespace surk;
 
 namespace {
 
-constexpr int64_t kPredictChunk = 65536;  // rows per forward pass of sur_predict
-constexpr int kMaxSplitK = 16;            // layers of a weight-gradient product
-constexpr int kSplitKRows = 256;          // batch rows per layer at least
+constexpr int64_t kWorkspaceRows = 65536;  // rows the workspace holds at least (sur_workspace_bytes as ever)
 
 struct Work {
   float *p, *m, *v, *g;
   uint16_t *wt1, *wt2, *wt3, *wb2, *wb3;
   float* w4f;
-  // one batch (max(max_batch, kPredictChunk) rows for the hidden activations)
-  float *z1, *z2, *z3;
-  uint16_t *h1, *h2, *h3, *dza, *dzb;
-  float *y, *r, *dy, *partial, *loss;
-  // split-K layers of the weight-gradient products
-  float* splitk;
+  // one training batch (TrainArgs)
+  uint16_t *XT, *h1T, *h2T, *h3T, *d1T, *d2T, *d3T;
+  float *r, *dy, *head_partial, *loss, *partial;
   // top-k scratch
   uint32_t *hist, *state, *blocks;
   int64_t blocks_cap;
@@ -40,7 +35,6 @@ struct Work {
 
 struct sur_handle {
   sur_config cfg{};
-  int64_t rows = 0;  // activation rows held by the workspace
   size_t bytes = 0;
   char* base = nullptr;
   Work w{};
@@ -88,7 +82,7 @@ static size_t layout(const sur_handle* h, char* base, Work* w) {
     off += bytes;
     return p;
   };
-  const int64_t R = h->rows;
+  const int64_t R = std::max<int64_t>(h->cfg.max_batch, kWorkspaceRows);
   const int64_t nblk_cap = (int64_t(1) << 31) / kTopkBlock + 1;
   Work x{};
   x.p = (float*)take(sizeof(float) * kNParams);
@@ -101,20 +95,18 @@ static size_t layout(const sur_handle* h, char* base, Work* w) {
   x.wb2 = (uint16_t*)take(2 * kHid * kHid);
   x.wb3 = (uint16_t*)take(2 * kHid * kHid);
   x.w4f = (float*)take(sizeof(float) * kHid);
-  x.z1 = (float*)take(sizeof(float) * R * kHid);
-  x.z2 = (float*)take(sizeof(float) * R * kHid);
-  x.z3 = (float*)take(sizeof(float) * R * kHid);
-  x.h1 = (uint16_t*)take(2 * R * kHid);
-  x.h2 = (uint16_t*)take(2 * R * kHid);
-  x.h3 = (uint16_t*)take(2 * R * kHid);
-  x.dza = (uint16_t*)take(2 * R * kHid);
-  x.dzb = (uint16_t*)take(2 * R * kHid);
-  x.y = (float*)take(sizeof(float) * R);
+  x.XT = (uint16_t*)take(2 * train_block_words(R, kFeat));
+  x.h1T = (uint16_t*)take(2 * train_block_words(R, kHid));
+  x.h2T = (uint16_t*)take(2 * train_block_words(R, kHid));
+  x.h3T = (uint16_t*)take(2 * train_block_words(R, kHid));
+  x.d1T = (uint16_t*)take(2 * train_block_words(R, kHid));
+  x.d2T = (uint16_t*)take(2 * train_block_words(R, kHid));
+  x.d3T = (uint16_t*)take(2 * train_block_words(R, kHid));
   x.r = (float*)take(sizeof(float) * R);
   x.dy = (float*)take(sizeof(float) * R);
-  x.partial = (float*)take(sizeof(float) * ((R + kHeadChunk - 1) / kHeadChunk) * (kHid + 2));
+  x.head_partial = (float*)take(sizeof(float) * ((R + kHeadChunk - 1) / kHeadChunk) * (kHid + 2));
   x.loss = (float*)take(sizeof(float) * 4);
-  x.splitk = (float*)take(sizeof(float) * kMaxSplitK * (kHid + 1) * kHid);
+  x.partial = (float*)take(sizeof(float) * kMaxSplitK * kOffW4);
   x.hist = (uint32_t*)take(sizeof(uint32_t) * 256);
   x.state = (uint32_t*)take(sizeof(uint32_t) * 4);
   x.blocks = (uint32_t*)take(sizeof(uint32_t) * 3 * nblk_cap);
@@ -137,7 +129,6 @@ int sur_create(const sur_config* cfg, sur_handle** out) {
     return fail(nullptr, SUR_E_INVALID, "Adam settings out of range (lr > 0, 0 <= beta < 1, eps > 0)");
   sur_handle* h = new sur_handle();
   h->cfg = *cfg;
-  h->rows = cfg->max_batch > kPredictChunk ? cfg->max_batch : kPredictChunk;
   h->bytes = layout(h, nullptr, nullptr);
   *out = h;
   return SUR_OK;
@@ -184,47 +175,6 @@ int sur_features(sur_handle* h, int64_t n, const int32_t* nh, const int8_t* pare
   return SUR_OK;
 }
 
-// Forward pass over rows [0, n) of a chunk: layers into the workspace, then the head.
-static int forward_rows(sur_handle* h, int n, const uint16_t* X, int64_t x_rows, const int32_t* idx, bool keep_z,
-                        hipStream_t s) {
-  const Work& w = h->w;
-  GemmArgs a{};
-  a.N = kHid;
-  a.onesRow = -1;
-  a.ldc = kHid;
-  // layer 1: X[idx] (n x 128) * W1
-  a.M = n;
-  a.K = kFeat;
-  a.A = X;
-  a.lda = kFeat;
-  a.gatherA = idx;
-  a.rowsA = x_rows;
-  a.B = w.wt1;
-  a.ldb = kFeat;
-  a.bias = w.p + kOffB1;
-  a.zout = keep_z ? w.z1 : nullptr;
-  a.hout = w.h1;
-  SUR_HIP(h, gemm(kRowK, kRowK, kEpiGelu, a, s), "layer 1");
-  // layers 2, 3
-  a.K = kHid;
-  a.lda = kHid;
-  a.gatherA = nullptr;
-  a.ldb = kHid;
-  a.A = w.h1;
-  a.B = w.wt2;
-  a.bias = w.p + kOffB2;
-  a.zout = keep_z ? w.z2 : nullptr;
-  a.hout = w.h2;
-  SUR_HIP(h, gemm(kRowK, kRowK, kEpiGelu, a, s), "layer 2");
-  a.A = w.h2;
-  a.B = w.wt3;
-  a.bias = w.p + kOffB3;
-  a.zout = keep_z ? w.z3 : nullptr;
-  a.hout = w.h3;
-  SUR_HIP(h, gemm(kRowK, kRowK, kEpiGelu, a, s), "layer 3");
-  return SUR_OK;
-}
-
 int sur_predict(sur_handle* h, int64_t n, const uint16_t* X, int64_t x_rows, const int32_t* idx, float* y,
                 void* stream) {
   int rc = ready(h);
@@ -257,66 +207,36 @@ int sur_adam_step(sur_handle* h, const float* grad, void* stream) {
 static int train_step(sur_handle* h, int B, const uint16_t* X, int64_t x_rows, const float* target,
                       const int32_t* idx, float* loss, hipStream_t s) {
   const Work& w = h->w;
-  int rc = forward_rows(h, B, X, x_rows, idx, true, s);
-  if (rc) return rc;
-  // head: y, dy, dz3; then grad W4, b4 and the loss
-  SUR_HIP(h, head(B, w.h3, w.w4f, w.p + kOffB4, w.y, target, idx, x_rows, w.z3, w.r, w.dy, w.dza, s), "head");
-  SUR_HIP(h, head_reduce(B, w.h3, w.dy, w.r, w.partial, w.g + kOffW4, w.g + kOffB4, loss ? loss : w.loss, s),
-          "head reduce");
-  GemmArgs a{};
-  // grad [W3; b3] = [h2 | 1]^T dz3   (M = 257 rows: the last one sums dz3 for the bias)
-  a.M = kHid + 1;
-  a.N = kHid;
-  a.K = B;
-  a.A = w.h2;
-  a.lda = kHid;
-  a.onesRow = kHid;
-  a.B = w.dza;
-  a.ldb = kHid;
-  a.fout = w.g + kOffW3;
-  a.ldc = kHid;
-  // the batch (the reduction) is long and M x N small: split it over layers
-  a.ksplit = std::min(kMaxSplitK, std::max(1, B / kSplitKRows));
-  a.partial = w.splitk;
-  SUR_HIP(h, gemm(kRowM, kRowM, kEpiF32, a, s), "grad W3");
-  // dz2 = bf16((dz3 W3^T) * GELU'(z2))
-  GemmArgs d{};
-  d.M = B;
-  d.N = kHid;
-  d.K = kHid;
-  d.A = w.dza;
-  d.lda = kHid;
-  d.onesRow = -1;
-  d.B = w.wb3;
-  d.ldb = kHid;
-  d.zin = w.z2;
-  d.ldz = kHid;
-  d.hout = w.dzb;
-  d.ldc = kHid;
-  SUR_HIP(h, gemm(kRowK, kRowK, kEpiGeluGrad, d, s), "dz2");
-  a.A = w.h1;
-  a.B = w.dzb;
-  a.fout = w.g + kOffW2;
-  SUR_HIP(h, gemm(kRowM, kRowM, kEpiF32, a, s), "grad W2");
-  d.A = w.dzb;
-  d.B = w.wb2;
-  d.zin = w.z1;
-  d.hout = w.dza;
-  SUR_HIP(h, gemm(kRowK, kRowK, kEpiGeluGrad, d, s), "dz1");
-  // grad [W1; b1] = [X[idx] | 1]^T dz1
-  a.M = kFeat + 1;
-  a.A = X;
-  a.lda = kFeat;
-  a.gatherA = idx;
-  a.rowsA = x_rows;
-  a.onesRow = kFeat;
-  a.B = w.dza;
-  a.fout = w.g + kOffW1;
-  SUR_HIP(h, gemm(kRowM, kRowM, kEpiF32, a, s), "grad W1");
+  TrainArgs a{};
+  a.B = B;
+  a.x_rows = x_rows;
+  a.X = X;
+  a.idx = idx;
+  a.target = target;
+  a.p = w.p;
+  a.w4 = w.w4f;
+  a.wt1 = w.wt1;
+  a.wt2 = w.wt2;
+  a.wt3 = w.wt3;
+  a.wb2 = w.wb2;
+  a.wb3 = w.wb3;
+  a.r = w.r;
+  a.dy = w.dy;
+  a.XT = w.XT;
+  a.h1T = w.h1T;
+  a.h2T = w.h2T;
+  a.h3T = w.h3T;
+  a.d1T = w.d1T;
+  a.d2T = w.d2T;
+  a.d3T = w.d3T;
+  a.partial = w.partial;
+  a.head_partial = w.head_partial;
+  a.g = w.g;
+  a.loss = loss ? loss : w.loss;
   h->t += 1;
-  SUR_HIP(h, adam(w.p, w.m, w.v, w.g, h->t, h->cfg.lr, h->cfg.beta1, h->cfg.beta2, h->cfg.eps, w.wt1, w.wt2, w.wt3,
-                  w.wb2, w.wb3, w.w4f, s),
-          "adam");
+  SUR_HIP(h, train(a, w.p, w.m, w.v, h->t, h->cfg.lr, h->cfg.beta1, h->cfg.beta2, h->cfg.eps, w.wt1, w.wt2, w.wt3,
+                   w.wb2, w.wb3, w.w4f, s),
+          "training step");
   return SUR_OK;
 }
 

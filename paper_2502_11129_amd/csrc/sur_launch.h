@@ -25,35 +25,37 @@ constexpr int kHeadChunk = 128;
 // Elements per block of the top-k compaction.
 constexpr int kTopkBlock = 1024;
 
-enum ALayout { kRowK = 0, kRowM = 1 };      // stored row = m (k contiguous) | stored row = k (m contiguous)
-enum Epilogue { kEpiGelu = 0, kEpiGeluGrad = 1, kEpiF32 = 2 };
+// Layers of batch rows a weight-gradient product is split over, and rows per layer at least.
+constexpr int kMaxSplitK = 16;
+constexpr int kSplitKRows = 256;
 
-// C = A B (+ epilogue) on BF16 MFMA with FP32 accumulation.
-struct GemmArgs {
-  int M, N, K;
-  const uint16_t* A;
-  int lda;
-  const int32_t* gatherA;  // optional: stored row r of A is gatherA[r]
-  int64_t rowsA;           // with gatherA: stored rows available; other indices read as NaN
-  int onesRow;             // logical row m == onesRow of A is all ones (-1: none)
-  const uint16_t* B;
-  int ldb;
-  // epilogues
-  const float* bias;  // kEpiGelu: z = acc + bias[n]
-  float* zout;        // kEpiGelu: optional z
-  uint16_t* hout;     // kEpiGelu: bf16 GELU(z); kEpiGeluGrad: bf16(acc * GELU'(zin))
-  const float* zin;   // kEpiGeluGrad
-  int ldz;
-  float* fout;        // kEpiF32
-  int ldc;
-  // kEpiF32 only: split the reduction dimension K over `ksplit` workgroup
-  // layers; layer z writes its partial product to partial + z * M * N (row
-  // stride N) and a second pass sums the layers in order into fout
-  int ksplit;
-  float* partial;
+// One training step: B batch rows, row i at X[idx[i]] (x_rows stored rows, other
+// indices read as NaN) with target[idx[i]].
+struct TrainArgs {
+  int B;
+  int64_t x_rows;
+  const uint16_t* X;
+  const int32_t* idx;
+  const float* target;
+  // parameters and BF16 weights: forward wt_l[out][in], backward wb_l[in][out]
+  const float *p, *w4;
+  const uint16_t *wt1, *wt2, *wt3, *wb2, *wb3;
+  // workspace: residual and dL/dy per row; features, activations and their
+  // gradients in transposed blocks of 16 rows (train_block_words); partial sums
+  float *r, *dy;
+  uint16_t *XT, *h1T, *h2T, *h3T, *d1T, *d2T, *d3T;
+  float *partial, *head_partial;
+  // results: gradient of every parameter, mean squared residual
+  float *g, *loss;
+  // set by train(): layers of rows of the weight products, rows per layer, head chunks
+  int layers, kchunk, chunks;
 };
+// 16-bit words of a width-column matrix of R rows in transposed blocks.
+constexpr int64_t train_block_words(int64_t R, int width) { return (R + 31) / 32 * 32 * width; }
 
-hipError_t gemm(int alayout, int blayout, int epi, const GemmArgs& a, hipStream_t s);
+hipError_t train(const TrainArgs& a, float* p, float* m, float* v, int64_t t, double lr, double b1, double b2,
+                 double eps, uint16_t* wt1, uint16_t* wt2, uint16_t* wt3, uint16_t* wb2, uint16_t* wb3, float* w4f,
+                 hipStream_t s);
 
 // Predictions of n rows of X (x_rows stored rows; idx: optional gather, an index
 // outside gives NaN) in one launch: y = head(GELU layers), weights wt_l[out][in].
@@ -63,16 +65,6 @@ hipError_t predict(int64_t n, const uint16_t* X, int64_t x_rows, const int32_t* 
 
 hipError_t features(int64_t n, const int32_t* nh, const int8_t* parent, const int8_t* face, const int8_t* axis,
                     const float* cpg, uint16_t* X, hipStream_t s);
-
-// Prediction head y = h3 . w4 + b4.  Predict mode (target == NULL): y_out[i].
-// Training mode: y, r = y - target[idx[i]] (NaN when idx[i] is outside
-// [0, rows)), dy = 2 r / n, and the BF16
-// gradient of the last hidden pre-activation dz3 = bf16(dy w4 GELU'(z3)).
-hipError_t head(int n, const uint16_t* h3, const float* w4, const float* b4, float* y_out, const float* target,
-                const int32_t* idx, int64_t rows, const float* z3, float* r, float* dy, uint16_t* dz3, hipStream_t s);
-// Deterministic reductions of the head: grad W4, grad b4 and the loss.
-hipError_t head_reduce(int n, const uint16_t* h3, const float* dy, const float* r, float* partial, float* gW4,
-                       float* gb4, float* loss, hipStream_t s);
 
 hipError_t adam(float* p, float* m, float* v, const float* g, int64_t t, double lr, double b1, double b2, double eps,
                 uint16_t* wt1, uint16_t* wt2, uint16_t* wt3, uint16_t* wb2, uint16_t* wb3, float* w4f,
