@@ -146,8 +146,8 @@ int sur_topk(sur_handle* h, int64_t n, const float* scores, int64_t k, int32_t* 
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * selection as sur_topk, with the same result, without a handle or workspace.
- * Its scratch (histogram, selection state, per-block counts) is a static
- * device array of the library, SUR_TOPK_NOALLOC_MAX scores' worth (≈ 193 KiB),
+ * Its scratch (histogram, selection state, counts of up to 256 tiles) is a
+ * static device array of the library (≈ 1 MiB, enough for any n accepted),
  * one copy per GPU, held until the process ends; the call allocates nothing.
  * Every call on a GPU shares that GPU's copy: calls that overlap on one GPU
  * (concurrent streams, threads) race and must be serialised by the caller.

@@ -803,167 +803,286 @@ __device__ inline uint32_t score_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__global__ __launch_bounds__(256) void topk_init_kernel(uint32_t* hist, uint32_t* state, uint32_t k) {
-  hist[threadIdx.x] = 0;
-  if (threadIdx.x < 4) state[threadIdx.x] = threadIdx.x == 2 ? k : 0u;
-}
+// A radix select over digits of 11, 11 and 10 bits finds the k-th largest key T
+// (a wide first digit spreads scores of like size over many counters), then the
+// scores above T and the first of those equal to it go out in index order.
+// Bound by launches and, per pass, by the way to memory and back: 1 000 003
+// scores 37 us; 117 us with 8-bit digits, 2048 workgroups adding to one histogram,
+// a serial choice of the digit and a scan of the counts in launches of their own.
+// 8 keys a thread and round: with 4 65 536 scores take 26 us for 30 and 1 000 003
+// 39 for 37, with 16 they take 38 and 41.
+constexpr int kTkThreads = 1024, kTkWaves = kTkThreads / 64;
+constexpr int kTkKeys = 8;                        // keys of a thread in one round
+constexpr int kTkRound = kTkThreads * kTkKeys;
+constexpr int kTkBins = kTopkHistWords, kTkLast = 1024;  // bins of a pass, of the last one
 
-__global__ __launch_bounds__(256) void topk_hist_kernel(int64_t n, const float* __restrict__ s,
-                                                        const uint32_t* __restrict__ state, uint32_t* hist,
-                                                        int shift) {
-  __shared__ uint32_t lh[256];
-  const int t = threadIdx.x;
-  lh[t] = 0;
-  __syncthreads();
-  const uint32_t prefix = state[0], mask = state[1];
-  for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256) {
-    const uint32_t k = score_key(s[i]);
-    if ((k & mask) == prefix) atomicAdd(&lh[(k >> shift) & 255u], 1u);
+// Sum of v over the threads up to and with this one; *total over all threads.
+__device__ inline uint32_t thread_scan(uint32_t v, uint32_t* wave_sums, uint32_t* total) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t a = __shfl_up(v, off);
+    v += lane >= off ? a : 0u;
   }
   __syncthreads();
-  if (lh[t]) atomicAdd(&hist[t], lh[t]);
+  if (lane == 63) wave_sums[wave] = v;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kTkWaves; ++w) {
+    const uint32_t c = wave_sums[w];
+    before += w < wave ? c : 0u;
+    all += c;
+  }
+  *total = all;
+  return before + v;
 }
 
-// Pick the digit of the k-th largest key among those matching the prefix.
-__global__ __launch_bounds__(256) void topk_select_kernel(uint32_t* hist, uint32_t* state, int shift) {
-  __shared__ uint32_t c[256];
-  const int t = threadIdx.x;
-  c[t] = hist[t];
-  hist[t] = 0;
+// The digit of the left-th largest of the keys counted in c (this thread's bins
+// from the top: 2 of kTkBins, or 1 of kTkLast) and how many remain below it.
+template <int BINS>
+__device__ inline void choose_digit(const uint32_t (&c)[BINS / kTkThreads], uint32_t left, uint32_t* wave_sums,
+                                    uint32_t* chosen) {
+  constexpr int PER = BINS / kTkThreads;
+  uint32_t sum = 0, all;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) sum += c[q];
+  uint32_t above = thread_scan(sum, wave_sums, &all) - sum;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (above < left && left <= above + c[q]) {
+      chosen[0] = BINS - 1 - (int)threadIdx.x * PER - q;
+      chosen[1] = left - above;
+    }
+    above += c[q];
+  }
   __syncthreads();
+}
+
+// Writes the indices of one round's keys (thread t: base + 1024 j + t) that are
+// above T or among the first keq equal to it; rg and re count those before.
+template <int K>
+__device__ inline void emit(const uint32_t (&key)[K], int64_t base, int64_t n, uint32_t T, uint32_t keq, uint32_t* rg,
+                            uint32_t* re, uint32_t* counts, int32_t* __restrict__ out) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  constexpr int PER = K * kTkWaves / 64;
+  uint64_t gt[K], eq[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const bool in = base + j * kTkThreads + t < n;
+    gt[j] = __ballot(in && key[j] > T);
+    eq[j] = __ballot(in && key[j] == T);
+    if (lane == 0) counts[j * kTkWaves + wave] = (uint32_t)__popcll(gt[j]) | ((uint32_t)__popcll(eq[j]) << 16);
+  }
+  __syncthreads();
+  // exclusive sums over the waves in index order, at most 16384 of each kind
+  if (wave == 0) {
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      c[q] = counts[lane * PER + q];
+      sum += c[q];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t a = __shfl_up(inc, off);
+      inc += lane >= off ? a : 0u;
+    }
+    if (lane == 63) counts[K * kTkWaves] = inc;
+    uint32_t before = inc - sum;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      counts[lane * PER + q] = before;
+      before += c[q];
+    }
+  }
+  __syncthreads();
+  const uint64_t below = ((uint64_t)1 << lane) - 1;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const uint32_t c = counts[j * kTkWaves + wave];
+    const uint32_t g = *rg + (c & 0xffffu) + (uint32_t)__popcll(gt[j] & below);
+    const uint32_t e = *re + (c >> 16) + (uint32_t)__popcll(eq[j] & below);
+    const int32_t i = (int32_t)(base + j * kTkThreads + t);
+    if ((gt[j] >> lane) & 1) out[g + (e < keq ? e : keq)] = i;
+    else if (((eq[j] >> lane) & 1) && e < keq) out[g + e] = i;
+  }
+  const uint32_t all = counts[K * kTkWaves];
+  *rg += all & 0xffffu;
+  *re += all >> 16;
+  __syncthreads();
+}
+
+// Up to kTkThreads * K scores: keys in registers, counters in LDS.
+template <int K>
+__global__ __launch_bounds__(kTkThreads) void topk_single_kernel(int64_t n, const float* __restrict__ s, uint32_t k,
+                                                                 int32_t* __restrict__ out) {
+  __shared__ uint32_t hist[kTkBins], counts[K * kTkWaves + 1], wave_sums[kTkWaves], chosen[2];
+  const int t = threadIdx.x;
+  uint32_t key[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) key[j] = j * kTkThreads + t < n ? score_key(s[j * kTkThreads + t]) : 0u;
+  uint32_t T = 0, left = k;
+#pragma unroll
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    for (int q = t; q < kTkBins; q += kTkThreads) hist[q] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+      if (j * kTkThreads + t < n && (pass == 0 || key[j] >> (pass == 1 ? 21 : 10) == T))
+        atomicAdd(&hist[(key[j] >> shift) & (pass == 2 ? kTkLast - 1 : kTkBins - 1)], 1u);
+    __syncthreads();
+    if (pass < 2) {
+      const uint32_t c[2] = {hist[kTkBins - 1 - 2 * t], hist[kTkBins - 2 - 2 * t]};
+      choose_digit<kTkBins>(c, left, wave_sums, chosen);
+      T = T << 11 | chosen[0];
+    } else {
+      const uint32_t c[1] = {hist[kTkLast - 1 - t]};
+      choose_digit<kTkLast>(c, left, wave_sums, chosen);
+      T = T << 10 | chosen[0];
+    }
+    left = chosen[1];
+  }
+  uint32_t rg = 0, re = 0;
+  emit<K>(key, 0, n, T, left, &rg, &re, counts, out);
+}
+
+__global__ __launch_bounds__(kTkThreads) void topk_init_kernel(uint32_t* hist, uint32_t* state, uint32_t k) {
+  for (int q = threadIdx.x; q < kTkBins; q += kTkThreads) hist[q] = 0;
+  if (threadIdx.x < 3) state[threadIdx.x] = threadIdx.x == 1 ? k : 0u;
+}
+
+// Pass PASS over this workgroup's tile of scores: its counts join the histogram,
+// and the workgroup that finishes last picks the digit.  state: the key's bits
+// so far, how many of the keys that share them are taken, workgroups done.
+// The last pass also leaves, per tile and digit d, how many of its keys are
+// above (bits, d); the entry before digit 0's counts those at or above (bits, 0).
+template <int PASS>
+__global__ __launch_bounds__(kTkThreads) void topk_pass_kernel(int64_t n, const float* __restrict__ s, int64_t tile,
+                                                               uint32_t* hist, uint32_t* state, uint32_t* above) {
+  constexpr int BINS = PASS == 2 ? kTkLast : kTkBins, PER = BINS / kTkThreads;
+  constexpr int SHIFT = PASS == 0 ? 21 : PASS == 1 ? 10 : 0, TOP = PASS == 1 ? 21 : 10;
+  __shared__ uint32_t lh[BINS], wave_sums[kTkWaves], chosen[2], last;
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) lh[q * kTkThreads + t] = 0;
+  const uint32_t bits = state[0], left = state[1];
+  __syncthreads();
+  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
+  uint32_t higher = 0;
+  for (int64_t b = beg; b < end; b += kTkRound) {
+    uint32_t key[kTkKeys];
+#pragma unroll
+    for (int j = 0; j < kTkKeys; ++j) {
+      const int64_t i = b + j * kTkThreads + t;
+      key[j] = i < end ? score_key(s[i]) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kTkKeys; ++j) {
+      const bool in = b + j * kTkThreads + t < end;
+      if (in && (PASS == 0 || key[j] >> TOP == bits)) atomicAdd(&lh[(key[j] >> SHIFT) & (BINS - 1)], 1u);
+      if (PASS == 2) higher += in && key[j] >> TOP > bits;
+    }
+  }
+  __syncthreads();
+  uint32_t c[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int d = BINS - 1 - t * PER - q;
+    c[q] = lh[d];
+    if (c[q]) atomicAdd(&hist[d], c[q]);
+  }
+  if (PASS == 2) {
+    uint32_t all_higher, all;
+    thread_scan(higher, wave_sums, &all_higher);
+    const uint32_t upto = thread_scan(c[0], wave_sums, &all);
+    uint32_t* out = above + (size_t)blockIdx.x * (kTkLast + 1);
+    out[BINS - t] = all_higher + upto - c[0];  // digit BINS - 1 - t
+    if (t == 0) out[0] = all_higher + all;
+  }
+  // Only device-scope atomics pass between workgroups here (the rest is for the
+  // next launch), so it is enough that each wave's are done before the ticket; a
+  // device-scope fence would write back the L2 once per wave.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (t == 0) last = atomicAdd(&state[2], 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int d = BINS - 1 - t * PER - q;
+    c[q] = __hip_atomic_load(&hist[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    hist[d] = 0;
+  }
+  choose_digit<BINS>(c, left, wave_sums, chosen);
   if (t == 0) {
-    const uint32_t kleft = state[2];
-    uint32_t above = 0;
-    int d = 255;
-    for (; d > 0; --d) {
-      if (above + c[d] >= kleft) break;
-      above += c[d];
-    }
-    state[0] = state[0] | ((uint32_t)d << shift);
-    state[1] = state[1] | (255u << shift);
-    state[2] = kleft - above;
+    state[0] = bits << (PASS == 2 ? 10 : 11) | chosen[0];
+    state[1] = chosen[1];
+    state[2] = 0;
   }
 }
 
-// Inclusive scan of one value per thread over a 256-thread block.
-__device__ inline uint32_t block_scan(uint32_t v, uint32_t* sh) {
+__global__ __launch_bounds__(kTkThreads) void topk_write_kernel(int64_t n, const float* __restrict__ s, int64_t tile,
+                                                                const uint32_t* __restrict__ state,
+                                                                const uint32_t* __restrict__ above,
+                                                                int32_t* __restrict__ out) {
+  __shared__ uint32_t counts[kTkKeys * kTkWaves + 1], wave_sums[kTkWaves];
   const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const uint32_t a = t >= off ? sh[t - off] : 0u;
-    __syncthreads();
-    sh[t] += a;
-    __syncthreads();
+  const uint32_t T = state[0], keq = state[1], d = T & (kTkLast - 1);
+  // those of the tiles before: above T, and equal to it
+  uint32_t g = 0, e = 0, rg, re;
+  if (t < (int)blockIdx.x) {
+    const uint32_t* a = above + (size_t)t * (kTkLast + 1) + d;
+    g = a[1];
+    e = a[0] - g;
   }
-  const uint32_t r = sh[t];
-  __syncthreads();
-  return r;
-}
-
-// Per block of kTopkBlock scores: (#key > T, #key == T), packed as gt << 16 | eq.
-__global__ __launch_bounds__(256) void topk_count_kernel(int64_t n, const float* __restrict__ s,
-                                                         const uint32_t* __restrict__ state, uint32_t* blocks) {
-  __shared__ uint32_t sh[256];
-  const uint32_t T = state[0];
-  const int64_t base = (int64_t)blockIdx.x * kTopkBlock + 4 * threadIdx.x;
-  uint32_t gt = 0, eq = 0;
+  thread_scan(g, wave_sums, &rg);
+  thread_scan(e, wave_sums, &re);
+  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
+  for (int64_t b = beg; b < end; b += kTkRound) {
+    uint32_t key[kTkKeys];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (base + j < n) {
-      const uint32_t k = score_key(s[base + j]);
-      gt += k > T;
-      eq += k == T;
+    for (int j = 0; j < kTkKeys; ++j) {
+      const int64_t i = b + j * kTkThreads + t;
+      key[j] = i < end ? score_key(s[i]) : 0u;
     }
-  }
-  const uint32_t tot = block_scan((gt << 16) | eq, sh);
-  if (threadIdx.x == 255) blocks[blockIdx.x] = tot;
-}
-
-// Exclusive prefix over blocks of the greater and equal counts (one block).
-__global__ __launch_bounds__(256) void topk_scan_kernel(int64_t nb, uint32_t* blocks, uint32_t* pre) {
-  __shared__ uint32_t sh[256];
-  __shared__ uint32_t carry_gt, carry_eq;
-  const int t = threadIdx.x;
-  if (t == 0) carry_gt = carry_eq = 0;
-  __syncthreads();
-  for (int64_t b0 = 0; b0 < nb; b0 += 256) {
-    const int64_t b = b0 + t;
-    const uint32_t v = b < nb ? blocks[b] : 0u;
-    const uint32_t gt_in = block_scan(v >> 16, sh);
-    const uint32_t eq_in = block_scan(v & 0xffffu, sh);
-    const uint32_t cg = carry_gt, ce = carry_eq;
-    if (b < nb) {
-      pre[2 * b] = cg + gt_in - (v >> 16);
-      pre[2 * b + 1] = ce + eq_in - (v & 0xffffu);
-    }
-    __syncthreads();
-    if (t == 255) {
-      carry_gt = cg + gt_in;
-      carry_eq = ce + eq_in;
-    }
-    __syncthreads();
-  }
-}
-
-__global__ __launch_bounds__(256) void topk_write_kernel(int64_t n, const float* __restrict__ s,
-                                                         const uint32_t* __restrict__ state,
-                                                         const uint32_t* __restrict__ pre, int32_t* __restrict__ out) {
-  __shared__ uint32_t sh[256];
-  const uint32_t T = state[0], keq = state[2];
-  const int64_t base = (int64_t)blockIdx.x * kTopkBlock + 4 * threadIdx.x;
-  uint32_t key[4];
-  uint32_t gt = 0, eq = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    key[j] = base + j < n ? score_key(s[base + j]) : 0u;
-    const bool in = base + j < n;
-    gt += in && key[j] > T;
-    eq += in && key[j] == T;
-  }
-  const uint32_t inc = block_scan((gt << 16) | eq, sh);
-  uint32_t rg = pre[2 * blockIdx.x] + (inc >> 16) - gt;
-  uint32_t re = pre[2 * blockIdx.x + 1] + (inc & 0xffffu) - eq;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (base + j >= n) break;
-    if (key[j] > T) {
-      out[rg + (re < keq ? re : keq)] = (int32_t)(base + j);
-      ++rg;
-    } else if (key[j] == T) {
-      if (re < keq) out[rg + re] = (int32_t)(base + j);
-      ++re;
-    }
+    emit<kTkKeys>(key, b, end, T, keq, &rg, &re, counts, out);
   }
 }
 
 hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const TopkScratch& ws, hipStream_t s) {
   if (k <= 0 || n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, s, ws.hist, ws.state, (uint32_t)k);
-  const int64_t hb = (n + 255) / 256;
-  const unsigned hist_blocks = (unsigned)(hb < 2048 ? hb : 2048);
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    hipLaunchKernelGGL(topk_hist_kernel, dim3(hist_blocks), dim3(256), 0, s, n, scores, ws.state, ws.hist, shift);
-    hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(256), 0, s, ws.hist, ws.state, shift);
+  // One launch for five up to 16 384 scores: there one workgroup takes 14 us and
+  // the tiles 29.  With 32 keys a thread it would take 24 us for 32 768 (tiles
+  // 30), but 16 instead of 10 us for 1000; the short form takes 9 us for those.
+  if (n <= 16 * kTkThreads) {
+    if (n <= 4 * kTkThreads)
+      hipLaunchKernelGGL(topk_single_kernel<4>, dim3(1), dim3(kTkThreads), 0, s, n, scores, (uint32_t)k, out);
+    else
+      hipLaunchKernelGGL(topk_single_kernel<16>, dim3(1), dim3(kTkThreads), 0, s, n, scores, (uint32_t)k, out);
+    return hipGetLastError();
   }
-  const int64_t nb = (n + kTopkBlock - 1) / kTopkBlock;
-  uint32_t* counts = ws.blocks;
-  uint32_t* pre = ws.blocks + nb;
-  hipLaunchKernelGGL(topk_count_kernel, dim3((unsigned)nb), dim3(256), 0, s, n, scores, ws.state, counts);
-  hipLaunchKernelGGL(topk_scan_kernel, dim3(1), dim3(256), 0, s, nb, counts, pre);
-  hipLaunchKernelGGL(topk_write_kernel, dim3((unsigned)nb), dim3(256), 0, s, n, scores, ws.state, pre, out);
+  // whole rounds, as few as at most kTopkTiles tiles allow
+  const int64_t rounds = (n + kTkRound - 1) / kTkRound;
+  const int64_t tile = (rounds + kTopkTiles - 1) / kTopkTiles * kTkRound;
+  const dim3 grid((unsigned)((n + tile - 1) / tile)), block(kTkThreads);
+  hipLaunchKernelGGL(topk_init_kernel, dim3(1), block, 0, s, ws.hist, ws.state, (uint32_t)k);
+  hipLaunchKernelGGL(topk_pass_kernel<0>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_pass_kernel<1>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_pass_kernel<2>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_write_kernel, grid, block, 0, s, n, scores, tile, ws.state, ws.above, out);
   return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------- top-k without allocation
-// Scratch of topk_noalloc: the histogram (256 words), the state (4 words, padded
-// to 64) and the per-block counts and prefixes (3 words per kTopkBlock scores)
-// of one selection over at most kTopkStaticMax scores.  A file-scope device
-// array: each GPU the library runs on holds its own copy until the process
-// ends; every call on a GPU uses that GPU's copy, so calls that overlap on one
-// GPU race.  topk_init_kernel clears what must start at zero.
-constexpr int64_t kTopkStaticWords = 256 + 64 + 3 * (kTopkStaticMax / kTopkBlock);
+// Scratch of topk_noalloc: the histogram, the state (padded to 64 words) and the
+// tiles' counts of one selection.  A file-scope device array: each GPU the
+// library runs on holds its own copy until the process ends; every call on a GPU
+// uses that GPU's copy, so calls that overlap on one GPU race.  topk_init_kernel
+// clears what must start at zero.
+constexpr int64_t kTopkStaticWords = kTopkHistWords + 64 + kTopkAboveWords;
 static __device__ __align__(256) uint32_t scratch[kTopkStaticWords];
 
 namespace {
@@ -995,7 +1114,7 @@ hipError_t topk_noalloc(int64_t n, const float* scores, int64_t k, int32_t* out,
   uint32_t* base = nullptr;
   const hipError_t e = static_scratch(&base);
   if (e != hipSuccess) return e;
-  const TopkScratch ws{base, base + 256, base + 256 + 64};
+  const TopkScratch ws{base, base + kTopkHistWords, base + kTopkHistWords + 64};
   return topk(n, scores, k, out, ws, s);
 }
 

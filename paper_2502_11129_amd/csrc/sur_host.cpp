@@ -26,8 +26,7 @@ struct Work {
   uint16_t *XT, *h1T, *h2T, *h3T, *d1T, *d2T, *d3T;
   float *r, *dy, *head_partial, *loss, *partial;
   // top-k scratch
-  uint32_t *hist, *state, *blocks;
-  int64_t blocks_cap;
+  uint32_t *hist, *state, *above;
   double* stats;
 };
 
@@ -83,7 +82,6 @@ static size_t layout(const sur_handle* h, char* base, Work* w) {
     return p;
   };
   const int64_t R = std::max<int64_t>(h->cfg.max_batch, kWorkspaceRows);
-  const int64_t nblk_cap = (int64_t(1) << 31) / kTopkBlock + 1;
   Work x{};
   x.p = (float*)take(sizeof(float) * kNParams);
   x.m = (float*)take(sizeof(float) * kNParams);
@@ -107,10 +105,9 @@ static size_t layout(const sur_handle* h, char* base, Work* w) {
   x.head_partial = (float*)take(sizeof(float) * ((R + kHeadChunk - 1) / kHeadChunk) * (kHid + 2));
   x.loss = (float*)take(sizeof(float) * 4);
   x.partial = (float*)take(sizeof(float) * kMaxSplitK * kOffW4);
-  x.hist = (uint32_t*)take(sizeof(uint32_t) * 256);
+  x.hist = (uint32_t*)take(sizeof(uint32_t) * kTopkHistWords);
   x.state = (uint32_t*)take(sizeof(uint32_t) * 4);
-  x.blocks = (uint32_t*)take(sizeof(uint32_t) * 3 * nblk_cap);
-  x.blocks_cap = nblk_cap;
+  x.above = (uint32_t*)take(sizeof(uint32_t) * kTopkAboveWords);
   x.stats = (double*)take(sizeof(double) * 2);
   if (w) *w = x;
   return (off + 255) & ~size_t(255);
@@ -322,7 +319,7 @@ int sur_topk(sur_handle* h, int64_t n, const float* scores, int64_t k, int32_t* 
   if (n > 0x7fffffffLL) return fail(h, SUR_E_INVALID, "n must fit int32 indices");
   if (k == 0) return SUR_OK;
   if (!scores || !out) return fail(h, SUR_E_INVALID, "NULL array");
-  TopkScratch ws{h->w.hist, h->w.state, h->w.blocks};
+  TopkScratch ws{h->w.hist, h->w.state, h->w.above};
   SUR_HIP(h, topk(n, scores, k, out, ws, (hipStream_t)stream), "topk");
   return SUR_OK;
 }

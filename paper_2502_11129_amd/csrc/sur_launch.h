@@ -23,7 +23,9 @@ static_assert(kOffB4 + 1 == kNParams, "parameter layout");
 // Rows of the head reduction handled per block.
 constexpr int kHeadChunk = 128;
 // Elements per block of the top-k compaction.
-constexpr int kTopkBlock = 1024;
+constexpr int kTopkTiles = 256;
+constexpr int kTopkHistWords = 2048;
+constexpr int kTopkAboveWords = kTopkTiles * 1025;
 
 // Layers of batch rows a weight-gradient product is split over, and rows per layer at least.
 constexpr int kMaxSplitK = 16;
@@ -75,9 +77,9 @@ hipError_t refresh_copies(const float* p, uint16_t* wt1, uint16_t* wt2, uint16_t
 
 // Top-k: radix select of the threshold key, then an index-ordered compaction.
 struct TopkScratch {
-  uint32_t* hist;     // [256]
-  uint32_t* state;    // [4]: prefix, mask, k remaining, unused
-  uint32_t* blocks;   // [3 * nblocks]: per block (#greater << 16 | #equal), then exclusive prefixes (2 per block)
+  uint32_t* hist;   // [kTopkHistWords]
+  uint32_t* state;  // [4]: key bits so far, k remaining, workgroups done, unused
+  uint32_t* above;  // [kTopkAboveWords]: per tile and last digit, keys above
 };
 hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const TopkScratch& ws, hipStream_t s);
 // The same selection with its scratch in a static device array of the library
