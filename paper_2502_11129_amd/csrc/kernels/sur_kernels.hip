@@ -29,7 +29,26 @@ __device__ inline uint16_t f2bf(float f) {
 }
 __device__ inline float bf2f(uint32_t b) { return __uint_as_float((b & 0xffffu) << 16); }
 
-__device__ inline float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+// erff takes one of two ways at |x| = 1, a branch per value.  Where all of a
+// wave's values keep clear of it (near_zero), the argument's range is told to the
+// compiler, which leaves the one polynomial: the same results, 8 instructions.
+template <bool SMALL>
+__device__ inline float erf_half(float z) {
+  const float x = z * 0.70710678118654752f;
+  if (SMALL) __builtin_assume(__builtin_fabsf(x) < 1.0f);
+  return erff(x);
+}
+// |z| < 1.4 for all values of all lanes (false with a NaN among them)
+__device__ inline bool near_zero(const float (&z)[4]) {
+  const float m = __builtin_elementwise_maximum(
+      __builtin_elementwise_maximum(__builtin_fabsf(z[0]), __builtin_fabsf(z[1])),
+      __builtin_elementwise_maximum(__builtin_fabsf(z[2]), __builtin_fabsf(z[3])));
+  return __builtin_amdgcn_ballot_w64(!(m < 1.4f)) == 0;
+}
+template <bool SMALL>
+__device__ inline float gelu(float z) {
+  return 0.5f * z * (1.0f + erf_half<SMALL>(z));
+}
 
 constexpr uint16_t kOne = 0x3F80;
 constexpr uint16_t kNaN = 0x7FC0;
@@ -102,9 +121,15 @@ __device__ inline void tile_gelu(const f32x4 (&acc)[2][NT], const float* bias, u
     const float4 bv = *reinterpret_cast<const float4*>(&bias[c0 + m * 16 + 4 * g]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
+      const float z[4] = {acc[m][t][0] + bv.x, acc[m][t][1] + bv.y, acc[m][t][2] + bv.z, acc[m][t][3] + bv.w};
       uint2 o;
-      o.x = pack_bf16(gelu(acc[m][t][0] + bv.x), gelu(acc[m][t][1] + bv.y));
-      o.y = pack_bf16(gelu(acc[m][t][2] + bv.z), gelu(acc[m][t][3] + bv.w));
+      if (near_zero(z)) {
+        o.x = pack_bf16(gelu<true>(z[0]), gelu<true>(z[1]));
+        o.y = pack_bf16(gelu<true>(z[2]), gelu<true>(z[3]));
+      } else {
+        o.x = pack_bf16(gelu<false>(z[0]), gelu<false>(z[1]));
+        o.y = pack_bf16(gelu<false>(z[2]), gelu<false>(z[3]));
+      }
       *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) = o;
     }
   }
@@ -486,8 +511,9 @@ __device__ inline int64_t blk16(int64_t row, int col, int width) {
 }
 
 // GELU and its derivative from one erf.
+template <bool SMALL>
 __device__ inline void gelu_pair(float z, float* h, float* d) {
-  const float e1 = 1.0f + erff(z * 0.70710678118654752f);
+  const float e1 = 1.0f + erf_half<SMALL>(z);
   *h = 0.5f * z * e1;
   *d = 0.5f * e1 + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
@@ -564,12 +590,17 @@ void train_rows_kernel(TrainArgs a) {
       const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        float hv[4], dv[4];
+        float z[4], hv[4], dv[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          gelu_pair(acc[m][t][i] + bb[i], &hv[i], &dv[i]);
-          d[m][t][i] = dv[i];
+        for (int i = 0; i < 4; ++i) z[i] = acc[m][t][i] + bb[i];
+        if (near_zero(z)) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) gelu_pair<true>(z[i], &hv[i], &dv[i]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) gelu_pair<false>(z[i], &hv[i], &dv[i]);
         }
+        d[m][t] = f32x4{dv[0], dv[1], dv[2], dv[3]};
         *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) =
             make_uint2(pack_bf16(hv[0], hv[1]), pack_bf16(hv[2], hv[3]));
       }
