@@ -60,10 +60,11 @@ constexpr uint16_t kNaN = 0x7FC0;
 // activations go from layer to layer through LDS in BF16.  The products run
 // with the weights as the row operand, so a lane's four results are four
 // consecutive columns of one row and go to LDS as eight bytes.
-// 1 M rows: 600 us, 550 TFLOP/s; layer at a time, with the activations (1.5 KB a
-// row) through HBM, 1816 us.  10 007 rows: 17 us, 39 in four launches.  What bounds
-// it is the exact erf of 768 GELUs a row (20 to 46 VALU instructions each, by the
-// size of the argument), then the matrix cores.
+// 1 M rows: 472 us, 700 TFLOP/s; layer at a time, with the activations (1.5 KB a
+// row) through HBM, 1816 us.  10 007 rows: 16 us, 39 in four launches.  What bounds
+// it is the matrix cores (235 us at the rate products alone reach), the exact erf
+// of 768 GELUs a row (8 vector instructions each, up to 46 where values are large:
+// then 790 us) and the LDS reads, which the barriers of a layer keep apart.
 constexpr int kPredWaves = 8;
 constexpr int kXS = kFeat + 8, kHS = kHid + 8;  // LDS row strides in BF16 (16-byte aligned, banks spread)
 
@@ -113,25 +114,34 @@ __device__ inline void tile_product(const bf16x8 (&w)[2][KS], const uint16_t* ac
   }
 }
 
-// h = bf16(GELU(acc + bias)) into LDS.
-template <int NT>
-__device__ inline void tile_gelu(const f32x4 (&acc)[2][NT], const float* bias, uint16_t* h, int c0, int r16, int g) {
+// h = bf16(GELU(acc + bias)) into LDS, 16 rows.
+__device__ inline void tile_gelu(const f32x4 (&acc)[2][1], const float* bias, uint16_t* h, int c0, int r16, int g) {
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
     const float4 bv = *reinterpret_cast<const float4*>(&bias[c0 + m * 16 + 4 * g]);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const float z[4] = {acc[m][t][0] + bv.x, acc[m][t][1] + bv.y, acc[m][t][2] + bv.z, acc[m][t][3] + bv.w};
-      uint2 o;
-      if (near_zero(z)) {
-        o.x = pack_bf16(gelu<true>(z[0]), gelu<true>(z[1]));
-        o.y = pack_bf16(gelu<true>(z[2]), gelu<true>(z[3]));
-      } else {
-        o.x = pack_bf16(gelu<false>(z[0]), gelu<false>(z[1]));
-        o.y = pack_bf16(gelu<false>(z[2]), gelu<false>(z[3]));
-      }
-      *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) = o;
+    const float z[4] = {acc[m][0][0] + bv.x, acc[m][0][1] + bv.y, acc[m][0][2] + bv.z, acc[m][0][3] + bv.w};
+    uint2 o;
+    if (near_zero(z)) {
+      o.x = pack_bf16(gelu<true>(z[0]), gelu<true>(z[1]));
+      o.y = pack_bf16(gelu<true>(z[2]), gelu<true>(z[3]));
+    } else {
+      o.x = pack_bf16(gelu<false>(z[0]), gelu<false>(z[1]));
+      o.y = pack_bf16(gelu<false>(z[2]), gelu<false>(z[3]));
     }
+    *reinterpret_cast<uint2*>(&h[r16 * kHS + c0 + m * 16 + 4 * g]) = o;
+  }
+}
+
+// One layer of a tile, 16 rows at a time: while one of a SIMD's two waves has the
+// matrix cores the other forms its GELUs.
+template <int KS, int ST, int NT>
+__device__ inline void tile_layer(const bf16x8 (&w)[2][KS], const uint16_t* act, const float* bias, uint16_t* h, int c0,
+                                  int r16, int g) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    f32x4 acc[2][1];
+    tile_product<KS, ST, 1>(w, act + t * 16 * ST, r16, g, acc);
+    tile_gelu(acc, bias, h + t * 16 * kHS, c0, r16, g);
   }
 }
 
@@ -207,16 +217,12 @@ void predict_kernel(int64_t n, const uint16_t* __restrict__ X, int64_t x_rows, c
     uint16_t* ha = hs[cur];
     uint16_t* hb = hs[cur ^ 1];
     if (tile + gridDim.x < tiles) fetch(tile + gridDim.x);
-    f32x4 acc[2][NT];
-    tile_product<kFeat / 32, kXS, NT>(w1, xs, r16, g, acc);
-    tile_gelu<NT>(acc, bias[0], ha, c0, r16, g);
+    tile_layer<kFeat / 32, kXS, NT>(w1, xs, bias[0], ha, c0, r16, g);
     __syncthreads();
     if (tile + gridDim.x < tiles) stage();
-    tile_product<kHid / 32, kHS, NT>(w2, ha, r16, g, acc);
-    tile_gelu<NT>(acc, bias[1], hb, c0, r16, g);
+    tile_layer<kHid / 32, kHS, NT>(w2, ha, bias[1], hb, c0, r16, g);
     __syncthreads();
-    tile_product<kHid / 32, kHS, NT>(w3, hb, r16, g, acc);
-    tile_gelu<NT>(acc, bias[2], ha, c0, r16, g);
+    tile_layer<kHid / 32, kHS, NT>(w3, hb, bias[2], ha, c0, r16, g);
     __syncthreads();
     // head: one wave per row, lane l owns hidden units 4l .. 4l+3
 #pragma unroll
@@ -232,21 +238,29 @@ void predict_kernel(int64_t n, const uint16_t* __restrict__ X, int64_t x_rows, c
 }
 
 // Rows per tile: as few as still give every CU (256) at most one tile, since a
-// tile's latency is what a small call waits for; 48 beyond that (64 rows would
-// spill 15 of the 256 registers).
+// tile's latency is what a small call waits for.  Beyond that a tile of R rows
+// costs a CU about 0.11 us x (R + 6), so the size whose rounds cost least: at
+// 1 M rows 48, 64 and 96 rows take 500, 487 and 472 us, at 16 000 rows 22.3,
+// 18.5 and 21.7 us, at 50 000 rows 40.5, 41.6 and 44.8 us.
 hipError_t predict(int64_t n, const uint16_t* X, int64_t x_rows, const int32_t* idx, const uint16_t* wt1,
                    const uint16_t* wt2, const uint16_t* wt3, const float* b1, const float* b2, const float* b3,
                    const float* w4, const float* b4, float* y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   constexpr int64_t kCus = 256;
-  const int nt = n <= 16 * kCus ? 1 : n <= 32 * kCus ? 2 : 3;
+  int nt = n <= 16 * kCus ? 1 : 2;
+  if (n > 32 * kCus) {
+    auto cost = [&](int64_t c) { return (n + 16 * c * kCus - 1) / (16 * c * kCus) * (16 * c + 6); };
+    nt = 3;
+    for (int c : {4, 6})
+      if (cost(c) < cost(nt)) nt = c;
+  }
   const int64_t tiles = (n + 16 * nt - 1) / (16 * nt);
   const dim3 grid((unsigned)(tiles < kCus ? tiles : kCus)), block(64 * kPredWaves);
 #define SUR_PREDICT(NT)                                                                                              \
   case NT:                                                                                                           \
     hipLaunchKernelGGL((predict_kernel<NT>), grid, block, 0, s, n, X, x_rows, idx, wt1, wt2, wt3, b1, b2, b3, w4, b4, y); \
     break;
-  switch (nt) { SUR_PREDICT(1) SUR_PREDICT(2) SUR_PREDICT(3) }
+  switch (nt) { SUR_PREDICT(1) SUR_PREDICT(2) SUR_PREDICT(3) SUR_PREDICT(4) SUR_PREDICT(6) }
 #undef SUR_PREDICT
   return hipGetLastError();
 }

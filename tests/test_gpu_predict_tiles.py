@@ -41,3 +41,31 @@ def test_predictions_at_tile_edges(net, n):
     assert torch.isnan(yi[~ok]).all()
     full = s.predict(X).cpu()
     assert torch.equal(yi[ok], full[idx[ok].long()])
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 24576, 24577])
+def test_predictions_in_long_tiles(net, n):
+    """64- and 96-row tiles: the rows again and again, bit for bit the same."""
+    s, X, ref = net
+    rep = X.repeat(3, 1)[:n].contiguous()
+    out = torch.full((n + 64,), 7.0, device="cuda")
+    y = s.predict(rep, out=out[:n])
+    assert (out[n:] == 7.0).all()
+    assert torch.equal(y, s.predict(X).repeat(3)[:n])
+
+
+def test_predictions_do_not_depend_on_the_rows_beside():
+    """Which form of erf a wave takes depends on the rows of its tile: rows with
+    small arguments give the same bits alone and among rows with large ones."""
+    s = Surrogate(params=W.mlp_init(9), max_batch=64)
+    X = s.features(s.upload_genotypes(W.random_genotypes(3000, key=92)))
+    mixed = X.clone()
+    mixed[::3] *= 32.0
+    mixed[5::48] = float("nan")
+    y, ym = s.predict(X), s.predict(mixed)
+    same = (mixed == X).all(dim=1)
+    assert torch.equal(y[same], ym[same])
+    assert torch.isnan(ym[5::48]).all() and torch.isfinite(ym[same]).all()
+    large = s.predict(mixed[~same].contiguous())
+    assert torch.equal(large.nan_to_num(), ym[~same].nan_to_num())
+    s.close()
