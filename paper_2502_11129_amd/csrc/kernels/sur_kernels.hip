@@ -50,6 +50,15 @@ __device__ inline float gelu(float z) {
   return 0.5f * z * (1.0f + erf_half<SMALL>(z));
 }
 
+// Place of element (row, k) of a BF16 matrix that is an operand of products over
+// k, in the order of a wave's registers for them: 16 rows and 32 k after each
+// other, lane (row % 16, k / 8 % 4) with its eight k.  A wave's load then takes
+// 1 KB of whole lines; by rows of k it touched a line per lane, 64 where 8 do:
+// 10 007 predictions took 15.9 us instead of 10.2, a training batch 40 instead of 33.
+__device__ inline int64_t operand(int row, int64_t k, int rows) {
+  return (((k >> 5) * (rows / 16) + (row >> 4)) * 64 + ((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
+}
+
 constexpr uint16_t kOne = 0x3F80;
 constexpr uint16_t kNaN = 0x7FC0;
 
@@ -61,7 +70,7 @@ constexpr uint16_t kNaN = 0x7FC0;
 // with the weights as the row operand, so a lane's four results are four
 // consecutive columns of one row and go to LDS as eight bytes.
 // 1 M rows: 472 us, 700 TFLOP/s; layer at a time, with the activations (1.5 KB a
-// row) through HBM, 1816 us.  10 007 rows: 16 us, 39 in four launches.  What bounds
+// row) through HBM, 1816 us.  10 007 rows: 10 us, 39 in four launches.  What bounds
 // it is the matrix cores (235 us at the rate products alone reach), the exact erf
 // of 768 GELUs a row (8 vector instructions each, up to 46 where values are large:
 // then 790 us) and the LDS reads, which the barriers of a layer keep apart.
@@ -152,7 +161,7 @@ __device__ inline void load_weights(bf16x8 (&w)[2][KS], const uint16_t* wt, int 
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       w[m][ks] = __builtin_bit_cast(
-          bf16x8, *reinterpret_cast<const uint4*>(&wt[(c0 + m * 16 + r16) * (32 * KS) + ks * 32 + 8 * g]));
+          bf16x8, *reinterpret_cast<const uint4*>(&wt[operand(c0 + m * 16 + r16, ks * 32 + 8 * g, kHid)]));
 }
 
 template <int NT>
@@ -241,7 +250,8 @@ void predict_kernel(int64_t n, const uint16_t* __restrict__ X, int64_t x_rows, c
 // tile's latency is what a small call waits for.  Beyond that a tile of R rows
 // costs a CU about 0.11 us x (R + 6), so the size whose rounds cost least: at
 // 1 M rows 48, 64 and 96 rows take 500, 487 and 472 us, at 16 000 rows 22.3,
-// 18.5 and 21.7 us, at 50 000 rows 40.5, 41.6 and 44.8 us.
+// 18.5 and 21.7 us, at 50 000 rows 40.5, 41.6 and 44.8 us (with 5 us more for
+// the weights than they now take).
 hipError_t predict(int64_t n, const uint16_t* X, int64_t x_rows, const int32_t* idx, const uint16_t* wt1,
                    const uint16_t* wt2, const uint16_t* wt3, const float* b1, const float* b2, const float* b3,
                    const float* w4, const float* b4, float* y, hipStream_t s) {
@@ -444,20 +454,20 @@ struct Copies {
   float* w4f;
 };
 
-// wt_l[o][i] (forward operand) and wb_l[i][o] (backward operand) hold bf16(W_l[i][o]).
+// wt_l(o, i) (forward operand) and wb_l(i, o) (backward operand) hold bf16(W_l[i][o]).
 __device__ inline void write_copy(int i, float val, const Copies& c) {
   const uint16_t b = f2bf(val);
   if (i < kOffB1) {
     const int in = i / kHid, o = i % kHid;
-    c.wt1[o * kFeat + in] = b;
+    c.wt1[operand(o, in, kHid)] = b;
   } else if (i >= kOffW2 && i < kOffB2) {
     const int j = i - kOffW2, in = j / kHid, o = j % kHid;
-    c.wt2[o * kHid + in] = b;
-    c.wb2[j] = b;
+    c.wt2[operand(o, in, kHid)] = b;
+    c.wb2[operand(in, o, kHid)] = b;
   } else if (i >= kOffW3 && i < kOffB3) {
     const int j = i - kOffW3, in = j / kHid, o = j % kHid;
-    c.wt3[o * kHid + in] = b;
-    c.wb3[j] = b;
+    c.wt3[operand(o, in, kHid)] = b;
+    c.wb3[operand(in, o, kHid)] = b;
   } else if (i >= kOffW4 && i < kOffB4) {
     c.w4f[i - kOffW4] = bf2f(b);
   }
@@ -515,14 +525,8 @@ hipError_t refresh_copies(const float* p, uint16_t* wt1, uint16_t* wt2, uint16_t
 // weight-gradient products, the parameter update.  (Layer at a time it was
 // thirteen, 175 us a batch of 4096, most of it launches and single-block sums.)
 //
-// Activations, features and gradients that the weight products read are kept
-// in BF16 blocks of 16 rows, transposed: element (row, col) of a matrix of W
-// columns at ((row / 16) W + col) 16 + row % 16.  The products sum over rows, so
-// this is the order in which a lane wants its eight operands, and both sides
-// move whole lines.
-__device__ inline int64_t blk16(int64_t row, int col, int width) {
-  return ((row >> 4) * width + col) * 16 + (row & 15);
-}
+// Activations, features and gradients that the weight products (sums over batch
+// rows) read are kept in BF16 as their operands: a column is a row, a batch row a k.
 
 // GELU and its derivative from one erf.
 template <bool SMALL>
@@ -532,16 +536,16 @@ __device__ inline void gelu_pair(float z, float* h, float* d) {
   *d = 0.5f * e1 + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// An LDS tile of R rows (stride ST) to its transposed blocks at row0.
-template <int R, int ST, int W>
-__device__ inline void store_blocks(const uint16_t* tile, uint16_t* __restrict__ out, int64_t row0, int tid) {
-  for (int e = tid; e < W * (R / 8); e += 64 * kPredWaves) {
-    const int c = e % W, r = (e / W) * 8;
+// An LDS tile of 16 batch rows (stride ST) to its place in an operand of W rows.
+template <int ST, int W>
+__device__ inline void store_operand(const uint16_t* tile, uint16_t* __restrict__ out, int64_t row0, int tid) {
+  for (int e = tid; e < 2 * W; e += 64 * kPredWaves) {
+    const int c = (e >> 5) * 16 + (e & 15), r = ((e >> 4) & 1) * 8;
     uint32_t v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       v[j] = (uint32_t)tile[(r + 2 * j) * ST + c] | ((uint32_t)tile[(r + 2 * j + 1) * ST + c] << 16);
-    *reinterpret_cast<uint4*>(out + blk16(row0 + r, c, W)) = make_uint4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<uint4*>(out + operand(c, row0 + r, W)) = make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -551,9 +555,9 @@ __device__ inline void store_blocks(const uint16_t* tile, uint16_t* __restrict__
 // take the way back through the same LDS buffers.  Rows past the batch have zero
 // features and zero gradient.  Bound by the weights' way from L2 (590 KB a
 // workgroup) and the erf and exp of 768 units a row.  Six batches of 4096 (a
-// launch per layer and direction before, activations through HBM): 1053 -> 243 us
-// in the three launches, a batch 25 us here, 10 us in the weight gradients and
-// 6 us in the update.
+// launch per layer and direction before, activations through HBM): 1053 -> 199 us
+// in the three launches, a batch 16 us here, 11 us in the weight gradients and
+// 5 us in the update.
 __global__ __launch_bounds__(64 * kPredWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void train_rows_kernel(TrainArgs a) {
   constexpr int NT = 1, R = 16 * NT;
@@ -631,17 +635,17 @@ void train_rows_kernel(TrainArgs a) {
                        pack_bf16(v[m][t][2] * d[m][t][2], v[m][t][3] * d[m][t][3]));
   };
 
-  store_blocks<R, kXS, kFeat>(xs, a.XT, row0, tid);
+  store_operand<kXS, kFeat>(xs, a.XT, row0, tid);
   tile_product<kFeat / 32, kXS, NT>(w1, xs, r16, g, acc);
   load_weights(wb, a.wt3, c0, r16, g);
   activate(bias[0], hs[0], d1);
   __syncthreads();
-  store_blocks<R, kHS, kHid>(hs[0], a.h1T, row0, tid);
+  store_operand<kHS, kHid>(hs[0], a.h1T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wa, hs[0], r16, g, acc);
   load_weights(wa, a.wb3, c0, r16, g);
   activate(bias[1], hs[1], d2);
   __syncthreads();
-  store_blocks<R, kHS, kHid>(hs[1], a.h2T, row0, tid);
+  store_operand<kHS, kHid>(hs[1], a.h2T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wb, hs[1], r16, g, acc);
   load_weights(wb, a.wb2, c0, r16, g);
   activate(bias[2], hs[0], d3);
@@ -668,7 +672,7 @@ void train_rows_kernel(TrainArgs a) {
       }
     }
   }
-  store_blocks<R, kHS, kHid>(hs[0], a.h3T, row0, tid);
+  store_operand<kHS, kHid>(hs[0], a.h3T, row0, tid);
   __syncthreads();
   {
     f32x4 v[2][NT];
@@ -684,20 +688,20 @@ void train_rows_kernel(TrainArgs a) {
     put_grad(v, d3, hs[1]);
   }
   __syncthreads();
-  store_blocks<R, kHS, kHid>(hs[1], a.d3T, row0, tid);
+  store_operand<kHS, kHid>(hs[1], a.d3T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wa, hs[1], r16, g, acc);
   put_grad(acc, d2, hs[0]);
   __syncthreads();
-  store_blocks<R, kHS, kHid>(hs[0], a.d2T, row0, tid);
+  store_operand<kHS, kHid>(hs[0], a.d2T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wb, hs[0], r16, g, acc);
   put_grad(acc, d1, hs[1]);
   __syncthreads();
-  store_blocks<R, kHS, kHid>(hs[1], a.d1T, row0, tid);
+  store_operand<kHS, kHid>(hs[1], a.d1T, row0, tid);
 }
 
 // Weight gradients [W_l; b_l] = [h | 1]^T dz_l over layer z of the batch rows (a
 // ones row of the activation operand gives the bias gradient), 128 x 128 outputs
-// per workgroup, 64 x 64 per wave straight from the transposed blocks, the
+// per workgroup, 64 x 64 per wave straight from the operands, the
 // partial sums of each layer of rows in the flat parameter layout; in the last
 // workgroups the head's sums (W4, b4 and the squared residuals) over chunks of
 // kHeadChunk rows, each in row order.
@@ -723,9 +727,9 @@ __global__ __launch_bounds__(256) void train_grad_kernel(TrainArgs a) {
       uint4 hb[8];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const uint4* hp = reinterpret_cast<const uint4*>(a.h3T + blk16(m0 + min(m + 16 * u, last), tid, kHid));
-        hb[2 * u] = hp[0];
-        hb[2 * u + 1] = hp[1];
+        const int64_t row = m0 + min(m + 16 * u, last);
+        hb[2 * u] = *reinterpret_cast<const uint4*>(a.h3T + operand(tid, row, kHid));
+        hb[2 * u + 1] = *reinterpret_cast<const uint4*>(a.h3T + operand(tid, row + 8, kHid));
       }
 #pragma unroll
       for (int j = 0; j < 64; ++j) {
@@ -775,8 +779,8 @@ __global__ __launch_bounds__(256) void train_grad_kernel(TrainArgs a) {
     bf16x8 df[4], hf[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      df[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(d + blk16(row, n0 + i * 16 + r16, kHid)));
-      hf[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(h + blk16(row, m0 + i * 16 + r16, width)));
+      df[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(d + operand(n0 + i * 16 + r16, row, kHid)));
+      hf[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(h + operand(m0 + i * 16 + r16, row, width)));
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

@@ -39,11 +39,11 @@ struct TrainArgs {
   const uint16_t* X;
   const int32_t* idx;
   const float* target;
-  // parameters and BF16 weights: forward wt_l[out][in], backward wb_l[in][out]
+  // parameters and BF16 weights, in the order their products load them
   const float *p, *w4;
   const uint16_t *wt1, *wt2, *wt3, *wb2, *wb3;
   // workspace: residual and dL/dy per row; features, activations and their
-  // gradients in transposed blocks of 16 rows (train_block_words); partial sums
+  // gradients as operands of the weight products (train_block_words); partial sums
   float *r, *dy;
   uint16_t *XT, *h1T, *h2T, *h3T, *d1T, *d2T, *d3T;
   float *partial, *head_partial;
@@ -52,7 +52,7 @@ struct TrainArgs {
   // set by train(): layers of rows of the weight products, rows per layer, head chunks
   int layers, kchunk, chunks;
 };
-// 16-bit words of a width-column matrix of R rows in transposed blocks.
+// 16-bit words of a width-column matrix of R batch rows as an operand.
 constexpr int64_t train_block_words(int64_t R, int width) { return (R + 31) / 32 * 32 * width; }
 
 hipError_t train(const TrainArgs& a, float* p, float* m, float* v, int64_t t, double lr, double b1, double b2,
