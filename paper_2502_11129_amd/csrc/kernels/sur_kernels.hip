@@ -856,14 +856,14 @@ __device__ inline uint32_t score_key(float f) {
 // (a wide first digit spreads scores of like size over many counters), then the
 // scores above T and the first of those equal to it go out in index order.
 // Bound by launches and, per pass, by the way to memory and back: 1 000 003
-// scores 37 us; 117 us with 8-bit digits, 2048 workgroups adding to one histogram,
+// scores 29 us; 115 us with 8-bit digits, 2048 workgroups adding to one histogram,
 // a serial choice of the digit and a scan of the counts in launches of their own.
-// 8 keys a thread and round: with 4 65 536 scores take 26 us for 30 and 1 000 003
-// 39 for 37, with 16 they take 38 and 41.
+// 8 keys a thread and round: when 1 000 003 scores took 37 us, 4 and 16 keys took
+// 39 and 41.
 constexpr int kTkThreads = 1024, kTkWaves = kTkThreads / 64;
 constexpr int kTkKeys = 8;                        // keys of a thread in one round
 constexpr int kTkRound = kTkThreads * kTkKeys;
-constexpr int kTkBins = kTopkHistWords, kTkLast = 1024;  // bins of a pass, of the last one
+constexpr int kTkBins = kTopkHistWords / 3, kTkLast = 1024;  // bins of a pass, of the last one
 
 // Sum of v over the threads up to and with this one; *total over all threads.
 __device__ inline uint32_t thread_scan(uint32_t v, uint32_t* wave_sums, uint32_t* total) {
@@ -998,36 +998,66 @@ __global__ __launch_bounds__(kTkThreads) void topk_single_kernel(int64_t n, cons
   emit<K>(key, 0, n, T, left, &rg, &re, counts, out);
 }
 
-__global__ __launch_bounds__(kTkThreads) void topk_init_kernel(uint32_t* hist, uint32_t* state, uint32_t k) {
-  for (int q = threadIdx.x; q < kTkBins; q += kTkThreads) hist[q] = 0;
-  if (threadIdx.x < 3) state[threadIdx.x] = threadIdx.x == 1 ? k : 0u;
+__global__ __launch_bounds__(kTkThreads) void topk_init_kernel(uint32_t* hist) {
+  hist[blockIdx.x * kTkThreads + threadIdx.x] = 0;
 }
 
-// Pass PASS over this workgroup's tile of scores: its counts join the histogram,
-// and the workgroup that finishes last picks the digit.  state: the key's bits
-// so far, how many of the keys that share them are taken, workgroups done.
+// This thread's scores of the round at b, zero past the end.
+__device__ inline void load_round(float (&x)[kTkKeys], const float* __restrict__ s, int64_t b, int64_t end) {
+#pragma unroll
+  for (int j = 0; j < kTkKeys; ++j) {
+    const int64_t i = b + j * kTkThreads + threadIdx.x;
+    x[j] = i < end ? s[i] : 0.f;
+  }
+}
+
+// The key's leading bits after the first PASSES digits, and how many of the keys
+// that share them are taken: every workgroup picks the last of those digits from
+// the finished histogram while its scores are on their way (a pick by the workgroup
+// that finishes last would wait for its counts, a ticket and the histogram in turn,
+// 7 us a pass for 5); workgroup 0 leaves it for the pass after.
+template <int PASSES>
+__device__ inline void chosen_bits(const uint32_t* hist, uint32_t* state, uint32_t k, uint32_t* wave_sums,
+                                   uint32_t* chosen, uint32_t* bits, uint32_t* left) {
+  constexpr int BINS = PASSES == 3 ? kTkLast : kTkBins, PER = BINS / kTkThreads;
+  const uint32_t* h = hist + (PASSES - 1) * kTkBins + BINS - 1 - threadIdx.x * PER;
+  uint32_t c[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) c[q] = h[-q];
+  const uint32_t before = PASSES == 1 ? 0u : state[2 * PASSES - 4], from = PASSES == 1 ? k : state[2 * PASSES - 3];
+  choose_digit<BINS>(c, from, wave_sums, chosen);
+  *bits = before << (PASSES == 3 ? 10 : 11) | chosen[0];
+  *left = chosen[1];
+  if (PASSES < 3 && blockIdx.x == 0 && threadIdx.x == 0) {
+    state[2 * PASSES - 2] = *bits;
+    state[2 * PASSES - 1] = *left;
+  }
+}
+
+// Pass PASS over this workgroup's tile of scores: its counts join the histogram.
 // The last pass also leaves, per tile and digit d, how many of its keys are
 // above (bits, d); the entry before digit 0's counts those at or above (bits, 0).
 template <int PASS>
-__global__ __launch_bounds__(kTkThreads) void topk_pass_kernel(int64_t n, const float* __restrict__ s, int64_t tile,
-                                                               uint32_t* hist, uint32_t* state, uint32_t* above) {
+__global__ __launch_bounds__(kTkThreads) void topk_pass_kernel(int64_t n, const float* __restrict__ s, uint32_t k,
+                                                               int64_t tile, uint32_t* hist, uint32_t* state,
+                                                               uint32_t* above) {
   constexpr int BINS = PASS == 2 ? kTkLast : kTkBins, PER = BINS / kTkThreads;
   constexpr int SHIFT = PASS == 0 ? 21 : PASS == 1 ? 10 : 0, TOP = PASS == 1 ? 21 : 10;
-  __shared__ uint32_t lh[BINS], wave_sums[kTkWaves], chosen[2], last;
+  __shared__ uint32_t lh[BINS], wave_sums[kTkWaves], chosen[2];
   const int t = threadIdx.x;
+  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
+  float x[kTkKeys];
+  load_round(x, s, beg, end);
 #pragma unroll
   for (int q = 0; q < PER; ++q) lh[q * kTkThreads + t] = 0;
-  const uint32_t bits = state[0], left = state[1];
-  __syncthreads();
-  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
-  uint32_t higher = 0;
+  uint32_t bits = 0, left = k, higher = 0;
+  if constexpr (PASS > 0) chosen_bits<PASS>(hist, state, k, wave_sums, chosen, &bits, &left);
+  else __syncthreads();
   for (int64_t b = beg; b < end; b += kTkRound) {
     uint32_t key[kTkKeys];
 #pragma unroll
-    for (int j = 0; j < kTkKeys; ++j) {
-      const int64_t i = b + j * kTkThreads + t;
-      key[j] = i < end ? score_key(s[i]) : 0u;
-    }
+    for (int j = 0; j < kTkKeys; ++j) key[j] = score_key(x[j]);
+    load_round(x, s, b + kTkRound, end);
 #pragma unroll
     for (int j = 0; j < kTkKeys; ++j) {
       const bool in = b + j * kTkThreads + t < end;
@@ -1041,7 +1071,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_pass_kernel(int64_t n, const 
   for (int q = 0; q < PER; ++q) {
     const int d = BINS - 1 - t * PER - q;
     c[q] = lh[d];
-    if (c[q]) atomicAdd(&hist[d], c[q]);
+    if (c[q]) atomicAdd(&hist[PASS * kTkBins + d], c[q]);
   }
   if (PASS == 2) {
     uint32_t all_higher, all;
@@ -1051,52 +1081,33 @@ __global__ __launch_bounds__(kTkThreads) void topk_pass_kernel(int64_t n, const 
     out[BINS - t] = all_higher + upto - c[0];  // digit BINS - 1 - t
     if (t == 0) out[0] = all_higher + all;
   }
-  // Only device-scope atomics pass between workgroups here (the rest is for the
-  // next launch), so it is enough that each wave's are done before the ticket; a
-  // device-scope fence would write back the L2 once per wave.
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (t == 0) last = atomicAdd(&state[2], 1u) == gridDim.x - 1;
-  __syncthreads();
-  if (!last) return;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int d = BINS - 1 - t * PER - q;
-    c[q] = __hip_atomic_load(&hist[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    hist[d] = 0;
-  }
-  choose_digit<BINS>(c, left, wave_sums, chosen);
-  if (t == 0) {
-    state[0] = bits << (PASS == 2 ? 10 : 11) | chosen[0];
-    state[1] = chosen[1];
-    state[2] = 0;
-  }
 }
 
-__global__ __launch_bounds__(kTkThreads) void topk_write_kernel(int64_t n, const float* __restrict__ s, int64_t tile,
-                                                                const uint32_t* __restrict__ state,
+__global__ __launch_bounds__(kTkThreads) void topk_write_kernel(int64_t n, const float* __restrict__ s, uint32_t k,
+                                                                int64_t tile, const uint32_t* hist, uint32_t* state,
                                                                 const uint32_t* __restrict__ above,
                                                                 int32_t* __restrict__ out) {
-  __shared__ uint32_t counts[kTkKeys * kTkWaves + 1], wave_sums[kTkWaves];
+  __shared__ uint32_t counts[kTkKeys * kTkWaves + 1], wave_sums[kTkWaves], chosen[2];
   const int t = threadIdx.x;
-  const uint32_t T = state[0], keq = state[1], d = T & (kTkLast - 1);
+  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
+  float x[kTkKeys];
+  load_round(x, s, beg, end);
+  uint32_t T, keq;
+  chosen_bits<3>(hist, state, k, wave_sums, chosen, &T, &keq);
   // those of the tiles before: above T, and equal to it
   uint32_t g = 0, e = 0, rg, re;
   if (t < (int)blockIdx.x) {
-    const uint32_t* a = above + (size_t)t * (kTkLast + 1) + d;
+    const uint32_t* a = above + (size_t)t * (kTkLast + 1) + (T & (kTkLast - 1));
     g = a[1];
     e = a[0] - g;
   }
   thread_scan(g, wave_sums, &rg);
   thread_scan(e, wave_sums, &re);
-  const int64_t beg = blockIdx.x * tile, end = beg + tile < n ? beg + tile : n;
   for (int64_t b = beg; b < end; b += kTkRound) {
     uint32_t key[kTkKeys];
 #pragma unroll
-    for (int j = 0; j < kTkKeys; ++j) {
-      const int64_t i = b + j * kTkThreads + t;
-      key[j] = i < end ? score_key(s[i]) : 0u;
-    }
+    for (int j = 0; j < kTkKeys; ++j) key[j] = score_key(x[j]);
+    load_round(x, s, b + kTkRound, end);
     emit<kTkKeys>(key, b, end, T, keq, &rg, &re, counts, out);
   }
 }
@@ -1104,8 +1115,8 @@ __global__ __launch_bounds__(kTkThreads) void topk_write_kernel(int64_t n, const
 hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const TopkScratch& ws, hipStream_t s) {
   if (k <= 0 || n <= 0) return hipSuccess;
   // One launch for five up to 16 384 scores: there one workgroup takes 14 us and
-  // the tiles 29.  With 32 keys a thread it would take 24 us for 32 768 (tiles
-  // 30), but 16 instead of 10 us for 1000; the short form takes 9 us for those.
+  // the tiles 22.  With 32 keys a thread it would take 24 us for 32 768 (tiles
+  // 22), and 16 instead of 10 us for 1000; the short form takes 9 us for those.
   if (n <= 16 * kTkThreads) {
     if (n <= 4 * kTkThreads)
       hipLaunchKernelGGL(topk_single_kernel<4>, dim3(1), dim3(kTkThreads), 0, s, n, scores, (uint32_t)k, out);
@@ -1117,11 +1128,12 @@ hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const T
   const int64_t rounds = (n + kTkRound - 1) / kTkRound;
   const int64_t tile = (rounds + kTopkTiles - 1) / kTopkTiles * kTkRound;
   const dim3 grid((unsigned)((n + tile - 1) / tile)), block(kTkThreads);
-  hipLaunchKernelGGL(topk_init_kernel, dim3(1), block, 0, s, ws.hist, ws.state, (uint32_t)k);
-  hipLaunchKernelGGL(topk_pass_kernel<0>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
-  hipLaunchKernelGGL(topk_pass_kernel<1>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
-  hipLaunchKernelGGL(topk_pass_kernel<2>, grid, block, 0, s, n, scores, tile, ws.hist, ws.state, ws.above);
-  hipLaunchKernelGGL(topk_write_kernel, grid, block, 0, s, n, scores, tile, ws.state, ws.above, out);
+  hipLaunchKernelGGL(topk_init_kernel, dim3(kTopkHistWords / kTkThreads), block, 0, s, ws.hist);
+  const uint32_t kk = (uint32_t)k;
+  hipLaunchKernelGGL(topk_pass_kernel<0>, grid, block, 0, s, n, scores, kk, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_pass_kernel<1>, grid, block, 0, s, n, scores, kk, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_pass_kernel<2>, grid, block, 0, s, n, scores, kk, tile, ws.hist, ws.state, ws.above);
+  hipLaunchKernelGGL(topk_write_kernel, grid, block, 0, s, n, scores, kk, tile, ws.hist, ws.state, ws.above, out);
   return hipGetLastError();
 }
 

@@ -24,7 +24,7 @@ static_assert(kOffB4 + 1 == kNParams, "parameter layout");
 constexpr int kHeadChunk = 128;
 // Elements per block of the top-k compaction.
 constexpr int kTopkTiles = 256;
-constexpr int kTopkHistWords = 2048;
+constexpr int kTopkHistWords = 3 * 2048;  // a histogram per pass
 constexpr int kTopkAboveWords = kTopkTiles * 1025;
 
 // Layers of batch rows a weight-gradient product is split over, and rows per layer at least.
@@ -78,7 +78,7 @@ hipError_t refresh_copies(const float* p, uint16_t* wt1, uint16_t* wt2, uint16_t
 // Top-k: radix select of the threshold key, then an index-ordered compaction.
 struct TopkScratch {
   uint32_t* hist;   // [kTopkHistWords]
-  uint32_t* state;  // [4]: key bits so far, k remaining, workgroups done, unused
+  uint32_t* state;  // [4]: after the first and the second digit, key bits and how many keys with them are taken
   uint32_t* above;  // [kTopkAboveWords]: per tile and last digit, keys above
 };
 hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const TopkScratch& ws, hipStream_t s);
