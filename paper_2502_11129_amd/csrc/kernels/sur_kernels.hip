@@ -155,13 +155,16 @@ __device__ inline void tile_layer(const bf16x8 (&w)[2][KS], const uint16_t* act,
 }
 
 template <int KS>
+__device__ inline void load_weights(bf16x8 (&w)[KS], const uint16_t* wt, int c0, int r16, int g) {
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    w[ks] = __builtin_bit_cast(bf16x8,
+                               *reinterpret_cast<const uint4*>(&wt[operand(c0 + r16, ks * 32 + 8 * g, kHid)]));
+}
+template <int KS>
 __device__ inline void load_weights(bf16x8 (&w)[2][KS], const uint16_t* wt, int c0, int r16, int g) {
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      w[m][ks] = __builtin_bit_cast(
-          bf16x8, *reinterpret_cast<const uint4*>(&wt[operand(c0 + m * 16 + r16, ks * 32 + 8 * g, kHid)]));
+  for (int m = 0; m < 2; ++m) load_weights(w[m], wt, c0 + m * 16, r16, g);
 }
 
 template <int NT>
@@ -555,8 +558,8 @@ __device__ inline void store_operand(const uint16_t* tile, uint16_t* __restrict_
 // take the way back through the same LDS buffers.  Rows past the batch have zero
 // features and zero gradient.  Bound by the weights' way from L2 (590 KB a
 // workgroup) and the erf and exp of 768 units a row.  Six batches of 4096 (a
-// launch per layer and direction before, activations through HBM): 1053 -> 199 us
-// in the three launches, a batch 16 us here, 11 us in the weight gradients and
+// launch per layer and direction before, activations through HBM): 1053 -> 180 us
+// in the three launches, a batch 15 us here, 9 us in the weight gradients and
 // 5 us in the update.
 __global__ __launch_bounds__(64 * kPredWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void train_rows_kernel(TrainArgs a) {
@@ -571,37 +574,46 @@ void train_rows_kernel(TrainArgs a) {
   const int c0 = 32 * wave;
   const int64_t row0 = (int64_t)blockIdx.x * R;
 
-  for (int e = tid; e < R * (kFeat / 8); e += T) {
-    const int r = e >> 4, c = e & 15;
-    const int64_t row = row0 + r;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row < a.B) {
-      const int64_t src = a.idx[row];
-      if (src >= 0 && src < a.x_rows) v = *reinterpret_cast<const uint4*>(a.X + src * kFeat + c * 8);
-      else v = make_uint4(kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u);
-    }
-    *reinterpret_cast<uint4*>(&xs[r * kXS + c * 8]) = v;
-  }
-  // the targets now: in the head their two dependent loads would stop every wave
-  if (tid >= T - R && row0 + tid - (T - R) < a.B) {
-    const int64_t ti = a.idx[row0 + tid - (T - R)];
-    ts[tid - (T - R)] = (ti >= 0 && ti < a.x_rows) ? a.target[ti] : __builtin_nanf("");
-  }
-  for (int e = tid; e < kHid; e += T) {
-    bias[0][e] = a.p[kOffB1 + e];
-    bias[1][e] = a.p[kOffB2 + e];
-    bias[2][e] = a.p[kOffB3 + e];
-    w4s[e] = a.w4[e];
-  }
+  // Half the threads take a 16-byte piece of a row each, sixteen others the
+  // targets (in the head their two dependent loads would stop every wave): first
+  // the indices, then what does not wait for them, then the rows.
+  static_assert(R * (kFeat / 8) <= T - R, "one piece per thread");
+  const int pr = tid < R * (kFeat / 8) ? tid >> 4 : tid >= T - R ? tid - (T - R) : -1;
+  const bool in = pr >= 0 && row0 + pr < a.B;
+  const int64_t src = in ? a.idx[row0 + pr] : -1;
   bf16x8 wa[2][kHid / 32], wb[2][kHid / 32], w1[2][kFeat / 32];
   load_weights(w1, a.wt1, c0, r16, g);
-  load_weights(wa, a.wt2, c0, r16, g);
+  float bv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (tid < kHid) {
+    bv[0] = a.p[kOffB1 + tid];
+    bv[1] = a.p[kOffB2 + tid];
+    bv[2] = a.p[kOffB3 + tid];
+    bv[3] = a.w4[tid];
+  }
   const float b4 = a.p[kOffB4];
+  const bool stored = src >= 0 && src < a.x_rows;
+  if (tid < R * (kFeat / 8)) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (stored) v = *reinterpret_cast<const uint4*>(a.X + src * kFeat + (tid & 15) * 8);
+    else if (in) v = make_uint4(kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u, kNaN * 0x10001u);
+    *reinterpret_cast<uint4*>(&xs[pr * kXS + (tid & 15) * 8]) = v;
+  } else if (tid >= T - R) {
+    ts[pr] = stored ? a.target[src] : __builtin_nanf("");
+  }
+  if (tid < kHid) {
+    bias[0][tid] = bv[0];
+    bias[1][tid] = bv[1];
+    bias[2][tid] = bv[2];
+    w4s[tid] = bv[3];
+  }
+  load_weights(wa, a.wt2, c0, r16, g);
   __syncthreads();
 
   f32x4 acc[2][NT], d1[2][NT], d2[2][NT], d3[2][NT];
-  // h = bf16(GELU(acc + b)) to LDS, GELU' to d
-  auto activate = [&](const float* b, uint16_t* h, f32x4 (&d)[2][NT]) {
+  // h = bf16(GELU(acc + b)) to LDS, GELU' to d, and the next weights for w on
+  // their way between: a layer's 128 KB keep the address unit busy for 2048 cycles,
+  // and a wave that asked for all of its part at once would wait for that first
+  auto activate = [&](const float* b, uint16_t* h, f32x4 (&d)[2][NT], bf16x8 (&w)[2][kHid / 32], const uint16_t* wt) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const float4 bv = *reinterpret_cast<const float4*>(&b[c0 + m * 16 + 4 * g]);
@@ -622,6 +634,9 @@ void train_rows_kernel(TrainArgs a) {
         *reinterpret_cast<uint2*>(&h[(t * 16 + r16) * kHS + c0 + m * 16 + 4 * g]) =
             make_uint2(pack_bf16(hv[0], hv[1]), pack_bf16(hv[2], hv[3]));
       }
+      __builtin_amdgcn_sched_barrier(0);
+      load_weights(w[m], wt, c0 + m * 16, r16, g);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   // dz = bf16(v * GELU') to LDS
@@ -637,18 +652,15 @@ void train_rows_kernel(TrainArgs a) {
 
   store_operand<kXS, kFeat>(xs, a.XT, row0, tid);
   tile_product<kFeat / 32, kXS, NT>(w1, xs, r16, g, acc);
-  load_weights(wb, a.wt3, c0, r16, g);
-  activate(bias[0], hs[0], d1);
+  activate(bias[0], hs[0], d1, wb, a.wt3);
   __syncthreads();
   store_operand<kHS, kHid>(hs[0], a.h1T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wa, hs[0], r16, g, acc);
-  load_weights(wa, a.wb3, c0, r16, g);
-  activate(bias[1], hs[1], d2);
+  activate(bias[1], hs[1], d2, wa, a.wb3);
   __syncthreads();
   store_operand<kHS, kHid>(hs[1], a.h2T, row0, tid);
   tile_product<kHid / 32, kHS, NT>(wb, hs[1], r16, g, acc);
-  load_weights(wb, a.wb2, c0, r16, g);
-  activate(bias[2], hs[0], d3);
+  activate(bias[2], hs[0], d3, wb, a.wb2);
   __syncthreads();
   // head: one wave per row, lane l owns hidden units 4l .. 4l+3
   {
@@ -702,7 +714,9 @@ void train_rows_kernel(TrainArgs a) {
 // Weight gradients [W_l; b_l] = [h | 1]^T dz_l over layer z of the batch rows (a
 // ones row of the activation operand gives the bias gradient), 128 x 128 outputs
 // per workgroup, 64 x 64 per wave straight from the operands, the
-// partial sums of each layer of rows in the flat parameter layout; in the last
+// partial sums of each layer of rows in the flat parameter layout (activations as
+// the row operand: a lane's results then lie in the columns beside its neighbours',
+// 16 lines a store and not 64, 1.7 us a batch of 4096 less); in the last
 // workgroups the head's sums (W4, b4 and the squared residuals) over chunks of
 // kHeadChunk rows, each in row order.
 constexpr int kHeadCols = kHid + 2;
@@ -785,8 +799,8 @@ __global__ __launch_bounds__(256) void train_grad_kernel(TrainArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], hf[j], acc[i][j], 0, 0, 0);
-      if (bias_row) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], ones, accb[i], 0, 0, 0);
+      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hf[j], df[i], acc[i][j], 0, 0, 0);
+      if (bias_row) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, df[i], accb[i], 0, 0, 0);
     }
   }
   float* out = a.partial + (size_t)z * kOffW4 + (prod == 2 ? kOffW3 : prod == 1 ? kOffW2 : kOffW1);
@@ -794,8 +808,9 @@ __global__ __launch_bounds__(256) void train_grad_kernel(TrainArgs a) {
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      *reinterpret_cast<f32x4*>(&out[(m0 + j * 16 + r16) * kHid + n0 + i * 16 + 4 * g]) = acc[i][j];
-    if (bias_row && r16 == 0) *reinterpret_cast<f32x4*>(&out[width * kHid + n0 + i * 16 + 4 * g]) = accb[i];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(m0 + j * 16 + 4 * g + r) * kHid + n0 + i * 16 + r16] = acc[i][j][r];
+    if (bias_row && g == 0) out[width * kHid + n0 + i * 16 + r16] = accb[i][0];
   }
 }
 
