@@ -875,7 +875,7 @@ __device__ __forceinline__ int row_min_i(int x) {
 // overflow contacts are built before the register ones, the free velocity is
 // not sunk below the contact rows.  With the LDS areas at most 1/8 of a CU's
 // 160 KB, 8192 quadrupeds x 500 steps take 25.6 ms (39.3 with one wave per
-// SIMD), 32768 boxes with a ball x 1000 steps 48.9 ms with three waves (66.1
+// SIMD), 32768 boxes with a ball x 1000 steps 48.9 ms with three waves (46.9 since; 66.1
 // with two, 113 with one).  12 contacts in registers, balls on the largest
 // robots and the tree-sparse inverse do not fit 256 and keep one wave.
 template <int NVC, int SB, int NCR, bool BALL, bool SELF, bool TREE>
