@@ -22,7 +22,7 @@ static_assert(kOffB4 + 1 == kNParams, "parameter layout");
 
 // Rows of the head reduction handled per block.
 constexpr int kHeadChunk = 128;
-// Elements per block of the top-k compaction.
+// Tiles of scores in a top-k selection, at most.
 constexpr int kTopkTiles = 256;
 constexpr int kTopkHistWords = 3 * 2048;  // a histogram per pass
 constexpr int kTopkAboveWords = kTopkTiles * 1025;
