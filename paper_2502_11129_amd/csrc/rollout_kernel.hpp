@@ -326,7 +326,7 @@ __device__ __forceinline__ void fmac3_bcast(const float (&m0)[1], const float (&
       "v_fmac_f32_dpp %0, -%3, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %1, -%4, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %2, -%5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf"
-      : "+v"(ya[0]), "+v"(yb[0]), "+v"(yc[0])
+      : "+&v"(ya[0]), "+&v"(yb[0]), "+&v"(yc[0])
       : "v"(xa), "v"(xb), "v"(xc), "v"(m0[0]), "v"(m1[0]), "v"(m2[0]), "v"(m3[0]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 template <int L>
@@ -357,7 +357,7 @@ __device__ __forceinline__ void fmac3_bcast(const float (&m0)[2], const float (&
       "v_fmac_f32_dpp %3, -%7, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %4, -%8, %15 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %5, -%8, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf"
-      : "+v"(ya[0]), "+v"(ya[1]), "+v"(yb[0]), "+v"(yb[1]), "+v"(yc[0]), "+v"(yc[1])
+      : "+&v"(ya[0]), "+&v"(ya[1]), "+&v"(yb[0]), "+&v"(yb[1]), "+&v"(yc[0]), "+&v"(yc[1])
       : "v"(xa), "v"(xb), "v"(xc), "v"(m0[0]), "v"(m0[1]), "v"(m1[0]), "v"(m1[1]), "v"(m2[0]), "v"(m2[1]), "v"(m3[0]), "v"(m3[1]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 
@@ -385,7 +385,7 @@ __device__ __forceinline__ void fmac1_bcast(const float (&m0)[1], const float (&
       "v_fmac_f32_dpp %0, -%1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %0, -%1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %0, -%1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-      : "+v"(ya[0])
+      : "+&v"(ya[0])
       : "v"(xa), "v"(m0[0]), "v"(m1[0]), "v"(m2[0]), "v"(m3[0]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 template <int L>
@@ -399,7 +399,7 @@ __device__ __forceinline__ void fmac1_bcast(const float (&m0)[2], const float (&
       "v_fmac_f32_dpp %1, -%2, %8 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %0, -%2, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %1, -%2, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
-      : "+v"(ya[0]), "+v"(ya[1])
+      : "+&v"(ya[0]), "+&v"(ya[1])
       : "v"(xa), "v"(m0[0]), "v"(m0[1]), "v"(m1[0]), "v"(m1[1]), "v"(m2[0]), "v"(m2[1]), "v"(m3[0]), "v"(m3[1]), "n"(L + 0), "n"(L + 1), "n"(L + 2), "n"(L + 3));
 }
 
