@@ -87,15 +87,17 @@ __device__ __forceinline__ float row_bcast(float x) {
 }
 
 // ----------------------------------------------------------------------------
-// Small 3D helpers.
+// Small 3D helpers.  SIMK_HD: also compiled for the host, where a test runs the
+// tests of a box pair on many pairs.
 // ----------------------------------------------------------------------------
+#define SIMK_HD __host__ __device__ __forceinline__
 struct f3 { float x, y, z; };
-__device__ __forceinline__ f3 mk(float a, float b, float c) { return {a, b, c}; }
-__device__ __forceinline__ f3 operator+(f3 a, f3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
-__device__ __forceinline__ f3 operator-(f3 a, f3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
-__device__ __forceinline__ f3 operator*(f3 a, float s) { return {a.x * s, a.y * s, a.z * s}; }
-__device__ __forceinline__ float dot3(f3 a, f3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
-__device__ __forceinline__ f3 cross3(f3 a, f3 b) {
+SIMK_HD f3 mk(float a, float b, float c) { return {a, b, c}; }
+SIMK_HD f3 operator+(f3 a, f3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
+SIMK_HD f3 operator-(f3 a, f3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
+SIMK_HD f3 operator*(f3 a, float s) { return {a.x * s, a.y * s, a.z * s}; }
+SIMK_HD float dot3(f3 a, f3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+SIMK_HD f3 cross3(f3 a, f3 b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 // 1/x from the hardware reciprocal (1 ulp) refined by one Newton step
@@ -137,7 +139,7 @@ struct m33 { float m[9]; };
 // weights (entries are finite): selects between elements of one array are
 // folded by the compiler into a dynamically indexed load, which would move R
 // into scratch memory
-__device__ __forceinline__ f3 mcol(const m33& R, int c) {
+SIMK_HD f3 mcol(const m33& R, int c) {
   const float w0 = c == 0 ? 1.f : 0.f, w1 = c == 1 ? 1.f : 0.f, w2 = c == 2 ? 1.f : 0.f;
   return {R.m[0] * w0 + R.m[1] * w1 + R.m[2] * w2, R.m[3] * w0 + R.m[4] * w1 + R.m[5] * w2,
           R.m[6] * w0 + R.m[7] * w1 + R.m[8] * w2};
@@ -146,7 +148,7 @@ __device__ __forceinline__ f3 mul(const m33& R, f3 v) {
   return {R.m[0] * v.x + R.m[1] * v.y + R.m[2] * v.z, R.m[3] * v.x + R.m[4] * v.y + R.m[5] * v.z,
           R.m[6] * v.x + R.m[7] * v.y + R.m[8] * v.z};
 }
-__device__ __forceinline__ f3 mulT(const m33& R, f3 v) {
+SIMK_HD f3 mulT(const m33& R, f3 v) {
   return {R.m[0] * v.x + R.m[3] * v.y + R.m[6] * v.z, R.m[1] * v.x + R.m[4] * v.y + R.m[7] * v.z,
           R.m[2] * v.x + R.m[5] * v.y + R.m[8] * v.z};
 }
@@ -547,13 +549,13 @@ __device__ __forceinline__ void put_contact(float* e, f3 x, unsigned plus, unsig
 }
 
 // A point x strictly inside a box (centre p, rotation R, half extents h).
-__device__ __forceinline__ bool point_in_box(f3 x, f3 p, const m33& R, f3 h) {
+SIMK_HD bool point_in_box(f3 x, f3 p, const m33& R, f3 h) {
   const f3 l = mulT(R, x - p);
   return fabsf(l.x) < h.x && fabsf(l.y) < h.y && fabsf(l.z) < h.z;
 }
 
 // Half-width of a box (rotation R, half extents h) along a unit direction u.
-__device__ __forceinline__ float box_radius(const m33& R, f3 h, f3 u) {
+SIMK_HD float box_radius(const m33& R, f3 h, f3 u) {
   return h.x * fabsf(u.x * R.m[0] + u.y * R.m[3] + u.z * R.m[6]) +
          h.y * fabsf(u.x * R.m[1] + u.y * R.m[4] + u.z * R.m[7]) +
          h.z * fabsf(u.x * R.m[2] + u.y * R.m[5] + u.z * R.m[8]);
@@ -562,10 +564,10 @@ __device__ __forceinline__ float box_radius(const m33& R, f3 h, f3 u) {
 // Least-overlap separating axis of boxes P and Q (P's face normals, Q's, then
 // the cross products of P's column i with Q's column j, normalised, skipped
 // when |cross|^2 < 1e-6; first smallest overlap wins), pointing from Q to P.
-__device__ __forceinline__ f3 sat_axis(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ) {
+SIMK_HD f3 sat_axis(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ) {
   const f3 d = pP - pQ;
   f3 best = mk(0.f, 0.f, 1.f);
-  float best_o = __int_as_float(0x7f800000);
+  float best_o = __builtin_inff();
   auto consider = [&](f3 u) {
     const float o = box_radius(RP, hP, u) + box_radius(RQ, hQ, u) - fabsf(dot3(u, d));
     if (o < best_o) { best_o = o; best = u; }
@@ -590,7 +592,7 @@ __device__ __forceinline__ f3 sat_axis(f3 pP, const m33& RP, f3 hP, f3 pQ, const
 // 1e-5 of their reach along it and 2e-6 of the coordinates' size (float rounding
 // of the overlap and of a corner's position is near 1e-7 of these): neither
 // sat_axis' least overlap nor a corner's side can come out otherwise.
-__device__ __forceinline__ bool boxes_apart(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ) {
+SIMK_HD bool boxes_apart(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ) {
   const f3 d = pP - pQ;
   const float slack = 1e-5f + 2e-6f * (fabsf(pP.x) + fabsf(pP.y) + fabsf(pP.z));
   bool apart = false;
@@ -606,7 +608,7 @@ __device__ __forceinline__ bool boxes_apart(f3 pP, const m33& RP, f3 hP, f3 pQ, 
 // An edge pair takes the contact from the face axes only when its overlap
 // beats the least face overlap by 1e-5 m plus 5 % of it (edges in parallel
 // planes give an edge-pair axis along the face normal with the same overlap).
-__device__ __forceinline__ bool edge_beats_face(float edge_o, float face_o) {
+SIMK_HD bool edge_beats_face(float edge_o, float face_o) {
   return edge_o < face_o - 1e-5f - 0.05f * face_o;
 }
 
@@ -617,11 +619,11 @@ __device__ __forceinline__ bool edge_beats_face(float edge_o, float face_o) {
 // the closest points of the two edges facing each other along it (P's on the
 // side of Q, Q's on the side of P), normal from Q towards P, depth the
 // overlap.  False in every other case.
-__device__ __forceinline__ bool edge_contact(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ, f3& x, f3& n,
+SIMK_HD bool edge_contact(f3 pP, const m33& RP, f3 hP, f3 pQ, const m33& RQ, f3 hQ, f3& x, f3& n,
                                              float& depth, int& face) {
   const f3 d = pP - pQ;
   f3 best = mk(0.f, 0.f, 1.f);
-  float best_o = __int_as_float(0x7f800000);
+  float best_o = __builtin_inff();
   int bi = -1, bj = -1;
   float fo[6];
   auto consider = [&](f3 u, int i, int j) {
@@ -634,7 +636,7 @@ __device__ __forceinline__ bool edge_contact(f3 pP, const m33& RP, f3 hP, f3 pQ,
 #pragma unroll
   for (int k = 0; k < 3; ++k) fo[3 + k] = consider(mcol(RQ, k), -1, -1);
   const float face_o = best_o;
-  float edge_o = __int_as_float(0x7f800000);
+  float edge_o = __builtin_inff();
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
@@ -770,7 +772,7 @@ __device__ __forceinline__ bool face_candidate(const FaceClip& F, int c, f3& x, 
 }
 
 // Corner c (bits x, y, z = signs) of a box with pose (R, p) and half extents h.
-__device__ __forceinline__ f3 box_corner(const m33& R, f3 p, f3 h, int c) {
+SIMK_HD f3 box_corner(const m33& R, f3 p, f3 h, int c) {
   const f3 s = mk((c & 1) ? h.x : -h.x, (c & 2) ? h.y : -h.y, (c & 4) ? h.z : -h.z);
   return mk(p.x + R.m[0] * s.x + R.m[1] * s.y + R.m[2] * s.z, p.y + R.m[3] * s.x + R.m[4] * s.y + R.m[5] * s.z,
             p.z + R.m[6] * s.x + R.m[7] * s.y + R.m[8] * s.z);
