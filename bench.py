@@ -126,7 +126,9 @@ def recorded_traffic(kernel, steps_per_launch):
     with open(src, "rb") as f:
         if hashlib.sha256(f.read()).hexdigest() != rec["kernel_source_sha256"]:
             return None
-    table = rec["per_launch_kib_by_steps_per_launch"].get(str(steps_per_launch), {})
+    # a kernel of one bin, or the kernel that runs all bins of a layout (keyed by the layout's bins)
+    table = {**rec["per_launch_kib_by_steps_per_launch"].get(str(steps_per_launch), {}),
+             **rec.get("one_launch_kib_by_steps_per_launch", {}).get(str(steps_per_launch), {})}
     if kernel not in table:
         return None
     fetch, write = table[kernel]
@@ -210,8 +212,8 @@ def main():
         options, trials = autotune(pop, T_pilot=T, log=lambda m: print(m, file=sys.stderr, flush=True))
     # per-bin launch timing (HIP events around each bin's launches) cannot be
     # recorded inside a captured graph and takes bins that go out in one launch
-    # apart: the rollouts are timed as a program runs them, and the per-kernel
-    # figures come from one more rollout of the same layout
+    # apart: the rollouts are timed as a program runs them, and the per-bin
+    # figures come from one more rollout (per_bin_options)
     sim = Simulator(pop, **options)
     stream = torch.cuda.current_stream()
     for _ in range(args.warmup):
@@ -239,7 +241,8 @@ def main():
         dst.copy_(src)
         torch.cuda.synchronize()
         del src, dst
-    sim_t = Simulator(pop, time_launches=True, **dict(options, use_graph=False))
+    one = sim.one_launch()
+    sim_t = Simulator(pop, **per_bin_options(options, one))
     sim_t.rollout(T)
     torch.cuda.synchronize()
     times, vb, bins, facs = sim_t.launch_times(), sim_t.variant_bins(), sim_t.bins(), sim_t.bin_factorization()
@@ -248,27 +251,13 @@ def main():
     fl_var = flops_per_variant(pop, T, rows_contact, rows_clamp,
                                factorization=np.array([facs[b] for b in vb]))
     fl = fl_var.sum()
-    # dominant kernel: the bin whose launches took longest in that rollout
-    # (HIP events around its launches on its own stream)
-    dom = int(np.argmax([t[0] for t in times]))
-    dom_ms, dom_launches = times[dom]
-    per_launch_s = dom_ms / 1e3 / max(dom_launches, 1)
-    dom_flops_per_launch = fl_var[vb == dom].sum() / max(dom_launches, 1)
-    achieved = dom_flops_per_launch / per_launch_s / 1e12
+    dom = dominant_kernel(one, bins, facs, vb, times, fl_var, ms_per_step, -(-T // (options.get("steps_per_launch") or 1000)),
+                          getattr(pop, "ball", None) is not None, bool(getattr(pop, "self_collision", False)))
+    achieved = dom["kernel_flops_per_launch"] / (dom["kernel_avg_launch_ms"] / 1e3) / 1e12
     all_bins = fl / (ms_per_step / 1e3) / 1e12
     byt = bytes_per_rollout(pop)
-    nvc, nbody, ncr, nvar = bins[dom]
-    ball = "true" if getattr(pop, "ball", None) is not None else "false"
-    selfc = "true" if getattr(pop, "self_collision", False) else "false"
-    tree = "true" if facs[dom] == "tree" else "false"
-    kernel_name = f"rollout_kernel<{nvc}, {nbody // 16}, {ncr}, {ball}, {selfc}, {tree}>"
-    if options.get("single_launch"):
-        # one kernel runs every bin: its launches carry the whole rollout
-        kernel_name = "rollout_multi_kernel"
-        nvar = pop.n_variants
-        dom_flops_per_launch = fl / max(dom_launches, 1)
-        achieved = dom_flops_per_launch / per_launch_s / 1e12
-    traffic = recorded_traffic(kernel_name, options.get("steps_per_launch") or 1000)
+    layout = "+".join(f"{b[0]}x{b[1] // 16}x{b[2]}" for b in sorted(bins))
+    traffic = recorded_traffic(dom["kernel"] + (f" {layout}" if one else ""), options.get("steps_per_launch") or 1000)
 
     out = {
         "metric": "variant-steps/sec at 1 MI355X",
@@ -291,12 +280,11 @@ def main():
                    "wall_s": wall},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP32_VECTOR_PEAK_TFLOPS, "traffic": traffic,
-                     "kernel": kernel_name,
-                     "kernel_variants": nvar, "kernel_launches_per_step": dom_launches,
-                     "kernel_avg_launch_ms": per_launch_s * 1e3,
-                     "kernel_flops_per_launch": dom_flops_per_launch,
+                     **dom,
                      "all_bins_achieved": all_bins, "all_bins_frac": all_bins / FP32_VECTOR_PEAK_TFLOPS,
                      "bin_ms_per_step": [round(t[0], 3) for t in times],
+                     "bin_ms_of": "each bin alone on the chip" if one and not options.get("single_launch")
+                     else "the timed layout",
                      "flops_per_step": fl, "hbm_bytes_per_step": byt,
                      "hbm_GBs": byt / (ms_per_step / 1e3) / 1e9},
     }
@@ -329,6 +317,34 @@ def main():
         out["roofline"]["frac_of_measured"] = achieved / peaks["fp32_fma_tflops"]
         out["roofline"]["all_bins_frac_of_measured"] = all_bins / peaks["fp32_fma_tflops"]
     print(json.dumps(out), flush=True)
+
+
+def per_bin_options(options, one):
+    """Options of the rollout that gives the bins' own times: the timed layout
+    with events around every bin's launches; where the timed rollouts send all
+    bins out in one launch, one bin after the other on one stream instead."""
+    o = dict(options, use_graph=False, time_launches=True)
+    if one and not o.get("single_launch"):
+        o["streams"] = 1
+    return o
+
+
+def dominant_kernel(one, bins, facs, vb, times, fl_var, ms_per_step, launches, ball, self_collision):
+    """The kernel that the timed rollouts spend most of their time in.  With all
+    bins in one launch it is the kernel of that launch: it carries the whole
+    rollout's flops over the measured time.  Otherwise the bin whose launches
+    took longest, by the events around them."""
+    if one:
+        return {"kernel": "rollout_multi_kernel", "kernel_variants": int(len(vb)), "kernel_launches_per_step": launches,
+                "kernel_avg_launch_ms": ms_per_step / launches, "kernel_flops_per_launch": float(fl_var.sum()) / launches}
+    dom = int(np.argmax([t[0] for t in times]))
+    ms, n = times[dom][0], max(times[dom][1], 1)
+    nvc, nbody, ncr, nvar = bins[dom]
+    flag = lambda x: "true" if x else "false"
+    return {"kernel": f"rollout_kernel<{nvc}, {nbody // 16}, {ncr}, {flag(ball)}, {flag(self_collision)}, "
+                      f"{flag(facs[dom] == 'tree')}>",
+            "kernel_variants": nvar, "kernel_launches_per_step": times[dom][1], "kernel_avg_launch_ms": ms / n,
+            "kernel_flops_per_launch": float(fl_var[vb == dom].sum()) / n}
 
 
 def rollout_spread(ms, vsteps):

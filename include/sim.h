@@ -328,6 +328,10 @@ int sim_chunk_plan(const sim_handle* h, size_t max_workspace_bytes, int32_t* n_c
  * only. */
 int sim_bin_factorization(const sim_handle* h, int32_t* n_bins, int32_t* factorization, int32_t max_bins);
 
+/* *one = 1 where the handle's bins go out together, in one launch per chunk of
+ * steps (single_launch, or chosen with streams = 0), else 0.  Host only. */
+int sim_one_launch(const sim_handle* h, int32_t* one);
+
 /* With time_launches set: per bin (in sim_bins order), the milliseconds
  * between the start of its first and the end of its last launch in the most
  * recent sim_step_batch / sim_rollout, and the number of launches (with

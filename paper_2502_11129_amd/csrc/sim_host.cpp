@@ -1244,6 +1244,12 @@ int sim_bin_factorization(const sim_handle* h, int32_t* n_bins, int32_t* factori
   return SIM_OK;
 }
 
+int sim_one_launch(const sim_handle* h, int32_t* one) {
+  if (!h || !one) return SIM_E_INVALID;
+  *one = h->multi ? 1 : 0;
+  return SIM_OK;
+}
+
 void sim_destroy(sim_handle* h) {
   if (!h) return;
   if (h->graph_exec) hipGraphExecDestroy(h->graph_exec);

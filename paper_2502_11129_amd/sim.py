@@ -19,7 +19,7 @@ SIM_ROOT_FREE, SIM_ROOT_FIXED = 0, 1
 SIM_HOST, SIM_DEVICE = 0, 1
 EXPORTED = ("sim_create", "sim_workspace_bytes", "sim_bind", "sim_step_batch", "sim_rollout", "sim_fitness",
             "sim_get_state", "sim_set_state", "sim_counters", "sim_rollout_split", "sim_rollout_host", "sim_bins",
-            "sim_variant_bins", "sim_bin_factorization", "sim_chunk_plan", "sim_launch_times", "sim_kernel_variants", "sim_split_allocation", "sim_plan_split", "sim_destroy", "sim_last_error")
+            "sim_variant_bins", "sim_bin_factorization", "sim_one_launch", "sim_chunk_plan", "sim_launch_times", "sim_kernel_variants", "sim_split_allocation", "sim_plan_split", "sim_destroy", "sim_last_error")
 
 _F = C.POINTER(C.c_float)
 _I32 = C.POINTER(C.c_int32)
@@ -118,6 +118,7 @@ def load():
     lib.sim_launch_times.argtypes = [P, _I32, _F, _I32, C.c_int32]
     lib.sim_variant_bins.argtypes = [P, _I32]
     lib.sim_bin_factorization.argtypes = [P, _I32, _I32, C.c_int32]
+    lib.sim_one_launch.argtypes = [P, _I32]
     lib.sim_chunk_plan.argtypes = [P, SZ, _I32, _I32, C.c_int32]
     lib.sim_split_allocation.argtypes = [C.c_int32, _I32, C.POINTER(C.c_double), C.c_int32, C.c_double, _I32, _I32,
                                          C.POINTER(C.c_double), C.POINTER(C.c_double)]
@@ -128,7 +129,7 @@ def load():
     lib.sim_last_error.restype = C.c_char_p
     for name in ("sim_workspace_bytes", "sim_bind", "sim_step_batch", "sim_rollout", "sim_fitness",
                  "sim_get_state", "sim_set_state", "sim_counters", "sim_bins", "sim_rollout_split",
-                 "sim_rollout_host", "sim_variant_bins", "sim_bin_factorization", "sim_chunk_plan", "sim_launch_times", "sim_kernel_variants", "sim_split_allocation", "sim_plan_split"):
+                 "sim_rollout_host", "sim_variant_bins", "sim_bin_factorization", "sim_one_launch", "sim_chunk_plan", "sim_launch_times", "sim_kernel_variants", "sim_split_allocation", "sim_plan_split"):
         getattr(lib, name).restype = I
     _lib = lib
     return lib
@@ -232,6 +233,12 @@ class Handle:
         f = np.zeros(64, np.int32)
         self._check(self.lib.sim_bin_factorization(self.h, C.byref(n), f.ctypes.data_as(_I32), 64))
         return [GPU_FACTORIZATIONS[int(x)] for x in f[:n.value]]
+
+    def one_launch(self) -> bool:
+        """Whether all bins go out in one launch per chunk of steps."""
+        one = C.c_int32()
+        self._check(self.lib.sim_one_launch(self.h, C.byref(one)))
+        return bool(one.value)
 
     def chunk_plan(self, max_workspace_bytes: int):
         """Ends of consecutive chunks (user order) whose handles each fit the workspace cap."""
