@@ -77,22 +77,61 @@ def autotune(pop, T_pilot=1000, reps=3, log=None, cache=None, min_gain=0.01, due
                 store = json.load(f)
             if key in store:
                 return store[key]["options"], store[key]["trials"]
-    trials = []
+    trials, tried, layouts = [], {}, {}
+    ball = getattr(pop, "ball", None) is not None
+    self_collision = bool(getattr(pop, "self_collision", False))
+
+    def layout_of(opts):
+        """How a handle with these options launches: its bins and their kernels,
+        and whether they go out together, on how many streams, in what launches."""
+        key = json.dumps(opts, sort_keys=True)
+        if key not in layouts:
+            h = S.Handle(pop, **opts)
+            bins, one, fac = h.bins(), h.one_launch(), h.bin_factorization()
+            h.close()
+            streams = 1 if one else min(opts.get("streams") or len(bins), len(bins))
+            layouts[key] = (tuple(bins), tuple(fac), one, streams, opts.get("steps_per_launch") or 1000,
+                            bool(opts.get("use_graph")))
+        return layouts[key]
 
     def run(opts):
-        t, bins = _time_rollout(pop, T_pilot, reps, **opts)
-        trials.append(dict(options=dict(opts), seconds=t, bins=bins))
-        if log:
-            log(f"autotune {opts}: {t * 1e3:.2f} ms, bins {[(b[0], b[1], b[2], b[3]) for b in bins]}")
-        return t
+        """Pilot time, once per layout: options that lead to the same launches are one trial."""
+        key = layout_of(opts)
+        if key not in tried:
+            t, bins = _time_rollout(pop, T_pilot, reps, **opts)
+            tried[key] = (t, dict(opts))
+            trials.append(dict(options=dict(opts), seconds=t, bins=bins))
+            if log:
+                log(f"autotune {opts}: {t * 1e3:.2f} ms, bins {[(b[0], b[1], b[2], b[3]) for b in bins]}")
+        return tried[key][0]
+
+    def budgets(best, best_t):
+        """Descent over the contact budget of each DoF capacity present, all in
+        the launch mode that `best` has: a budget that the one launch has no
+        kernel for would change the budget and the launches at once."""
+        one = layout_of(best)[2]
+        for nvc in sorted({b[0] for b in layout_of(best)[0]}):
+            for ncr in candidates_ncr(nvc, ball, self_collision):
+                if ncr == best["ncr_by_nvc"].get(nvc):
+                    continue
+                cand = dict(best, ncr_by_nvc={**best["ncr_by_nvc"], nvc: ncr})
+                try:
+                    if layout_of(cand)[2] != one:
+                        continue
+                    t = run(cand)
+                except S.SimError:
+                    continue                      # no kernel with that budget for this body capacity
+                if t < best_t * (1.0 - min_gain):
+                    best, best_t = cand, t
+        return best, best_t
 
     def descend(best, best_t):
         """Coordinate descent from a starting point: single launch, streams,
         launch length, hipGraph replay of the rollout's launches, the
-        contact budget of each DoF capacity present, then the tree-sparse
+        contact budget of each DoF capacity present (with all bins in one
+        launch, and with a launch per bin), then the tree-sparse
         factorisation."""
-        special = getattr(pop, "ball", None) is not None or bool(getattr(pop, "self_collision", False))
-        single = [] if special else [True]   # the multi-bin kernel has no ball or self-collision families
+        single = [] if ball or self_collision else [True]   # the multi-bin kernel has no such families
         for name, values in (("single_launch", single), ("streams", [4, 2, 1]), ("steps_per_launch", [250, 500]),
                              ("use_graph", [True])):
             for v in values:
@@ -105,52 +144,42 @@ def autotune(pop, T_pilot=1000, reps=3, log=None, cache=None, min_gain=0.01, due
                     continue                       # e.g. a bin outside the single-launch kernel
                 if t < best_t * (1.0 - min_gain):            # keep only clear wins
                     best, best_t = cand, t
-        probe = S.Handle(pop, **best)
-        nvcs = sorted({b[0] for b in probe.bins()})
-        probe.close()
-        for nvc in nvcs:
-            for ncr in candidates_ncr(nvc, getattr(pop, "ball", None) is not None,
-                                      bool(getattr(pop, "self_collision", False))):
-                if ncr == best["ncr_by_nvc"].get(nvc):
-                    continue
-                cand = dict(best, ncr_by_nvc={**best["ncr_by_nvc"], nvc: ncr})
-                try:
-                    t = run(cand)
-                except S.SimError:
-                    continue                      # no kernel with that budget for this body capacity
-                if t < best_t * (1.0 - min_gain):
-                    best, best_t = cand, t
-        # the tree-sparse factorisation, if some bin of this layout has it
-        cand = dict(best, gpu_factorization="tree")
-        probe = S.Handle(pop, **cand)
-        has_tree = "tree" in probe.bin_factorization()
-        probe.close()
-        if has_tree:
-            t = run(cand)
+        modes = [(best, best_t)]
+        if layout_of(best)[2]:
+            apart = dict({k: v for k, v in best.items() if k != "single_launch"}, streams=len(layout_of(best)[0]))
+            if not layout_of(apart)[2]:
+                modes.append((apart, run(apart)))
+        modes = [budgets(*m) for m in modes]
+        # the tree-sparse factorisation, if some bin of this layout has it (its
+        # kernels have launches of their own)
+        base, base_t = modes[-1]
+        cand = dict(base, gpu_factorization="tree")
+        if "tree" in layout_of(cand)[1]:
+            modes.append((cand, run(cand)))
+        best, best_t = modes[0]
+        for m, t in modes[1:]:
             if t < best_t * (1.0 - min_gain):
-                best, best_t = cand, t
+                best, best_t = m, t
         return best, best_t
 
-    # starting points: smallest body capacity per variant (more bins, some
-    # kernels with fewer registers), every variant in 32-body kernels (fewer
-    # bins), 32-body kernels only from 20 DoFs on with the smaller variants
-    # merged into one 16-DoF, 16-body bin (whose kernels run two waves per
-    # SIMD), and the same with the 20-DoF variants in 16-body kernels with 4
-    # contacts in registers (also two waves per SIMD); a start that gives the
-    # same bins as an earlier one is skipped
+    # starting points: smallest body capacity per variant (more bins, less work
+    # for padding), every variant in 32-body kernels (fewer bins), 32-body kernels
+    # only from 20 DoFs on with the smaller variants merged into one 16-DoF,
+    # 16-body bin, and the same with the 20-DoF variants in 16-body kernels with
+    # 4 contacts in registers; a start that gives the same bins as an earlier one
+    # is skipped
     results, seen = [], []
     for extra in (dict(min_body_slots=0), dict(min_body_slots=32),
                   dict(min_body_slots=32, slots32_min_nvc=20, min_nv_capacity=16),
                   dict(min_body_slots=32, slots32_min_nvc=24, min_nv_capacity=16, ncr_by_nvc={16: 8, 20: 4})):
         start_opts = dict(dict(streams=0, steps_per_launch=0, ncr_by_nvc={}), **extra)
-        probe = S.Handle(pop, **start_opts)
-        layout = sorted(tuple(b[:4]) for b in probe.bins())
-        probe.close()
+        layout = sorted(layout_of(start_opts)[0])
         if layout in seen:
             continue
         seen.append(layout)
         results.append(descend(start_opts, run(start_opts)))
     best, best_t = min(results, key=lambda r: r[1])
+    best = tried[layout_of(best)][1]
     close = []
     for tr in sorted(trials, key=lambda r: r["seconds"]):
         if tr["seconds"] <= best_t * (1.0 + duel_margin) and tr["options"] not in close:
