@@ -242,7 +242,7 @@ def main():
         torch.cuda.synchronize()
         del src, dst
     one = sim.one_launch()
-    sim_t = Simulator(pop, **per_bin_options(options, one))
+    sim_t = Simulator(pop, **per_bin_options(options, one, sim.bins()))
     sim_t.rollout(T)
     torch.cuda.synchronize()
     times, vb, bins, facs = sim_t.launch_times(), sim_t.variant_bins(), sim_t.bins(), sim_t.bin_factorization()
@@ -319,13 +319,15 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def per_bin_options(options, one):
+def per_bin_options(options, one, bins):
     """Options of the rollout that gives the bins' own times: the timed layout
     with events around every bin's launches; where the timed rollouts send all
-    bins out in one launch, one bin after the other on one stream instead."""
+    bins out in one launch, one bin after the other on one stream instead, with
+    the same contacts in registers."""
     o = dict(options, use_graph=False, time_launches=True)
     if one and not o.get("single_launch"):
         o["streams"] = 1
+        o["ncr_by_nvc"] = {b[0]: b[2] for b in bins}
     return o
 
 

@@ -149,9 +149,8 @@ typedef struct {
  * arithmetic in every configuration); they choose how the population is laid
  * out and launched, and are what the autotuner searches over.
  *  contacts_in_registers  contacts per variant whose solver rows stay in
- *                         registers, for every bin (0 = ncr_by_nvc, else the
- *                         first compiled kernel of the bin); contacts beyond
- *                         it spill to the workspace
+ *                         registers, for every bin (0 = ncr_by_nvc); contacts
+ *                         beyond it spill to the workspace
  *  use_graph              != 0: sim_rollout replays a captured hipGraph
  *  steps_per_launch       simulation steps per kernel launch (0 = 1000)
  *  streams                concurrent streams the bins are spread over, by
@@ -163,7 +162,10 @@ typedef struct {
  *                         variant; 32: every variant in 32-body kernels (fewer
  *                         bins)
  *  ncr_by_nvc[6]          per DoF capacity 8, 12, 16, 20, 24, 28: contacts in
- *                         registers (0 = the bin's first compiled kernel)
+ *                         registers (0 = chosen: the bin's first compiled
+ *                         kernel, or for plane bins of up to 16 DoFs the one
+ *                         with 16 where most robots can lie on more than 8
+ *                         corners or all bins go out in one launch)
  *  time_launches          != 0: every bin's launches are bracketed by HIP
  *                         events on the bin's stream (sim_launch_times)
  *  single_launch          != 0: all bins in one launch per chunk of steps, the

@@ -11,7 +11,7 @@
 namespace simk {
 
 #define SIMK_MULTI_FAMILIES(X)                                                                 \
-  X(8, 1, 8) X(12, 1, 8) X(16, 1, 8) X(16, 2, 8) X(16, 2, 16) X(20, 1, 4) X(20, 1, 8) X(20, 2, 8)  \
+  X(8, 1, 16) X(12, 1, 16) X(16, 1, 8) X(16, 1, 16) X(16, 2, 16) X(20, 1, 4) X(20, 1, 8) X(20, 2, 8)  \
   X(24, 1, 8) X(24, 2, 8) X(28, 2, 8)
 
 #define SIMK_MULTI_ENTRY(NVC, SB, NCR) {NVC, SB, NCR},

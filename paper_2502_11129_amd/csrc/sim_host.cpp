@@ -127,6 +127,69 @@ const KernelVariant* find_variant(int nvc, int sb, int ncr, int ball, int self) 
   return nullptr;
 }
 
+// Whether most of the listed robots (up to 64 of them, evenly spaced) can lie on
+// more than 8 corners: at the hinge angles of the initial state, with some face
+// direction of the core down, more than 8 corners are within 5 % of the core's
+// smallest half extent of the lowest.
+bool lies_on_many(const sim_model_desc& d, const std::vector<int>& users, const std::vector<int>& q_off) {
+  const int r0q = d.root_type == SIM_ROOT_FREE ? 7 : 0;
+  const size_t n = users.size(), step = (n + 63) / 64;
+  size_t seen = 0, many = 0;
+  for (size_t s = 0; s < n; s += step, ++seen) {
+    const int i = users[s], b0 = d.body_offset[i], nb = d.body_offset[i + 1] - b0;
+    if (4 * nb <= 8) continue;
+    double R[kMaxBodiesPerVariant][9], p[kMaxBodiesPerVariant][3];
+    std::vector<std::array<double, 3>> corners;
+    for (int b = 0; b < nb; ++b) {
+      const int g = b0 + b;
+      for (int k = 0; k < 9; ++k) R[b][k] = k % 4 == 0;
+      for (int k = 0; k < 3; ++k) p[b][k] = 0.0;
+      if (b > 0) {
+        // hinge: rest orientation, then the angle about the axis (Rodrigues)
+        const double* L = R[d.parent[g]];
+        const float *q = d.rest_quat + 4 * g, *u = d.axis + 3 * g, *ap = d.anchor_parent + 3 * g, *ac = d.anchor_child + 3 * g;
+        const double w = q[0], x = q[1], y = q[2], z = q[3], th = d.q0[q_off[i] + r0q + b - 1];
+        const double c = std::cos(th), t = std::sin(th), C = 1.0 - c;
+        const double E[9] = {1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y), 2 * (x * y + w * z), 1 - 2 * (x * x + z * z),
+                             2 * (y * z - w * x), 2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)};
+        const double H[9] = {c + u[0] * u[0] * C, u[0] * u[1] * C - u[2] * t, u[0] * u[2] * C + u[1] * t,
+                             u[1] * u[0] * C + u[2] * t, c + u[1] * u[1] * C, u[1] * u[2] * C - u[0] * t,
+                             u[2] * u[0] * C - u[1] * t, u[2] * u[1] * C + u[0] * t, c + u[2] * u[2] * C};
+        auto mul = [](const double* A, const double* B, double* out) {
+          for (int r = 0; r < 3; ++r)
+            for (int k = 0; k < 3; ++k) out[3 * r + k] = A[3 * r] * B[k] + A[3 * r + 1] * B[3 + k] + A[3 * r + 2] * B[6 + k];
+        };
+        double LE[9];
+        mul(L, E, LE);
+        mul(LE, H, R[b]);
+        for (int k = 0; k < 3; ++k)
+          p[b][k] = p[d.parent[g]][k] + L[3 * k] * ap[0] + L[3 * k + 1] * ap[1] + L[3 * k + 2] * ap[2] -
+                    (R[b][3 * k] * ac[0] + R[b][3 * k + 1] * ac[1] + R[b][3 * k + 2] * ac[2]);
+      }
+      const float* h = d.half_ext + 3 * g;
+      for (int cn = 0; cn < 8; ++cn) {
+        const double e[3] = {cn & 1 ? h[0] : -h[0], cn & 2 ? h[1] : -h[1], cn & 4 ? h[2] : -h[2]};
+        std::array<double, 3> at;
+        for (int k = 0; k < 3; ++k) at[k] = p[b][k] + R[b][3 * k] * e[0] + R[b][3 * k + 1] * e[1] + R[b][3 * k + 2] * e[2];
+        corners.push_back(at);
+      }
+    }
+    const float* h = d.half_ext + 3 * b0;
+    const double near = 0.05 * std::min({h[0], h[1], h[2]});
+    bool wide = false;
+    for (int dir = 0; dir < 6; ++dir) {
+      const double sign = dir < 3 ? 1.0 : -1.0;
+      double low = INFINITY;
+      int count = 0;
+      for (const auto& at : corners) low = std::min(low, sign * at[dir % 3]);
+      for (const auto& at : corners) count += sign * at[dir % 3] <= low + near;
+      wide = wide || count > 8;
+    }
+    many += wide;
+  }
+  return 2 * many > seen;
+}
+
 // Launch every bin's kernel for n_steps (reset on the first chunk if asked).
 // Bins are independent: bin 0 runs on the caller's stream, every other bin on
 // a library stream forked from and joined back into the caller's stream.
@@ -505,10 +568,25 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
   std::stable_sort(hp->bins.begin(), hp->bins.end(), [&](const Bin& x, const Bin& y) {
     return wave_cost(x) != wave_cost(y) ? wave_cost(x) > wave_cost(y) : cost(x) > cost(y);
   });
+  // Families of up to 16 DoFs, no budget asked for: the kernels with 8 contacts
+  // in registers run three waves per SIMD, those with 16 two.  Where most robots
+  // of a bin can lie on more than 8 corners, 16 are the faster at every size:
+  // chains of 4, 7 and 11 equal bricks lying flat, 4096 x 500 steps, take 13.3,
+  // 29.5 and 75.9 ms (8: 18.8, 45.3 and 89.3 ms), 16384 of them 34.0, 82.7 and
+  // 174.7 (46.0, 109.1 and 230.5).  Others, snakes on 3 to 4 contacts, are slower
+  // with 16: 16 snakes 7.5 ms (7.3), 32768 36.5 ms (29.3).  Bins that go out in
+  // one launch run two waves per SIMD anyway and have 16: 3000 trees of up to 16
+  // DoFs 11.5 ms (12.4).
+  auto wide_budget = [&](const Bin& b) -> const KernelVariant* {
+    if (ball || self || b.tree || b.nvc > 16 || ncr_for(b.nvc) > 0) return nullptr;
+    return find_variant(b.nvc, b.sb, 16, 0, 0);
+  };
   // single launch: every bin must be one of the multi-bin kernel's families
   auto find_multi = [&](Bin& b) {
+    const KernelVariant* kv = wide_budget(b);
+    const int ncr = kv ? kv->ncr : b.ncr;
     for (int k = 0; k < kNumMultiFamilies; ++k)
-      if (kMultiFamilies[k].nvc == b.nvc && kMultiFamilies[k].sb == b.sb && kMultiFamilies[k].ncr == b.ncr)
+      if (kMultiFamilies[k].nvc == b.nvc && kMultiFamilies[k].sb == b.sb && kMultiFamilies[k].ncr == ncr)
         b.multi_kind = k;
     return b.multi_kind >= 0;
   };
@@ -541,6 +619,12 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
       tree = tree || b.tree;
     }
     hp->multi = covered && !tree && (large || waves <= 2 * kSimds);
+  }
+  for (Bin& b : hp->bins) {
+    const KernelVariant* kv = wide_budget(b);
+    if (!kv || !(hp->multi || lies_on_many(*d, b.users, hp->q_off))) continue;
+    b.ncr = kv->ncr;
+    b.fn = kv->fn;
   }
   // streams: longest-first assignment of the bins to the least-loaded stream
   {

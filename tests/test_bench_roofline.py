@@ -32,6 +32,15 @@ def test_handle_tells_whether_the_bins_go_out_together(options, one):
     ball.close()
 
 
+def test_the_bins_alone_keep_their_contacts_in_registers():
+    pop = W.random_trees(8200)                            # more than two waves a SIMD: apart, the default would be 8
+    h = S.Handle(pop)
+    o = bench.per_bin_options({}, h.one_launch(), h.bins())
+    assert h.one_launch() and S.Handle(pop, **o).bins() == h.bins()
+    assert S.Handle(pop, streams=1).bins() != h.bins()
+    h.close()
+
+
 @pytest.mark.parametrize("options,kernel", [
     ({}, "rollout_multi_kernel"), (dict(TUNED, steps_per_launch=250), "rollout_multi_kernel"),
     (dict(min_body_slots=32, single_launch=True), "rollout_multi_kernel"),
@@ -40,9 +49,9 @@ def test_handle_tells_whether_the_bins_go_out_together(options, one):
 def test_kernel_and_time_of_the_timed_rollouts(options, kernel):
     pop, T, ms = W.random_trees(300), 1000, 50.0
     h = S.Handle(pop, **options)
-    one = h.one_launch()
+    one, timed = h.one_launch(), h.bins()
     h.close()
-    o = bench.per_bin_options(options, one)
+    o = bench.per_bin_options(options, one, timed)
     t = S.Handle(pop, **o)
     assert t.one_launch() is bool(o.get("single_launch")) and o["time_launches"]
     if not one:
