@@ -165,7 +165,7 @@ typedef struct {
  *                         registers (0 = chosen: the bin's first compiled
  *                         kernel, or for plane bins of up to 16 DoFs the one
  *                         with 16 where most robots can lie on more than 8
- *                         corners or all bins go out in one launch)
+ *                         corners, or go out in one launch with such a bin)
  *  time_launches          != 0: every bin's launches are bracketed by HIP
  *                         events on the bin's stream (sim_launch_times)
  *  single_launch          != 0: all bins in one launch per chunk of steps, the

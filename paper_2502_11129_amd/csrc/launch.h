@@ -24,11 +24,17 @@ extern const int kNumKernelVariants;
 extern const KernelVariant kTreeKernelVariants[];
 extern const int kNumTreeKernelVariants;
 
-// The multi-bin kernel: its family list (nvc, sb, ncr per kind index) and launcher.
+// The multi-bin kernels: each one's family list (nvc, sb, ncr per kind index) and
+// launcher.  Set 0 keeps 8 contacts in registers in the families of up to 16 DoFs
+// (and 16 in the one with 32 bodies), set 1 keeps 16.
 struct MultiFamily { int nvc, sb, ncr; };
-extern const MultiFamily kMultiFamilies[];
-extern const int kNumMultiFamilies;
-hipError_t launch_rollout_multi(const MultiArgs& m, const ModelParams& p, int blocks, hipStream_t st);
+struct MultiSet {
+  const MultiFamily* families;
+  int n;
+  hipError_t (*launch)(const MultiArgs& m, const ModelParams& p, int blocks, hipStream_t st);
+};
+const MultiSet& multi_set0();
+const MultiSet& multi_set1();
 
 // Device-side state transfer between a bin's packed layout and the caller's
 // variant-CSR arrays (map: int4 per packed variant, see state_kernels.hip).

@@ -96,7 +96,7 @@ struct sim_handle {
   std::vector<int> stream_of;             // bin -> stream index (0 = caller's)
   int n_streams = 1;
   int steps_per_launch = kStepsPerLaunch;
-  bool multi = false;                     // all bins in one launch per chunk
+  const MultiSet* multi = nullptr;        // the kernel that runs all bins in one launch per chunk, if they go so
 };
 
 namespace {
@@ -273,7 +273,7 @@ int launch_multi(sim_handle* h, int n_steps, bool reset, hipStream_t st, const s
       m.bin[i].n_steps = chunk;
       m.bin[i].reset = (reset && first) ? 1 : 0;
     }
-    hipError_t e = launch_rollout_multi(m, h->params, blocks, st);
+    hipError_t e = h->multi->launch(m, h->params, blocks, st);
     if (e != hipSuccess) return dev_check(h, e, "kernel launch");
     done += chunk;
     first = false;
@@ -574,30 +574,34 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
   // chains of 4, 7 and 11 equal bricks lying flat, 4096 x 500 steps, take 13.3,
   // 29.5 and 75.9 ms (8: 18.8, 45.3 and 89.3 ms), 16384 of them 34.0, 82.7 and
   // 174.7 (46.0, 109.1 and 230.5).  Others, snakes on 3 to 4 contacts, are slower
-  // with 16: 16 snakes 7.5 ms (7.3), 32768 36.5 ms (29.3).  Bins that go out in
-  // one launch run two waves per SIMD anyway and have 16: 3000 trees of up to 16
-  // DoFs 11.5 ms (12.4).
+  // with 16: 16 snakes 7.5 ms (7.3), 32768 36.5 ms (29.3).  A launch of several
+  // bins has 16 for all of them as soon as one such bin is there.
   auto wide_budget = [&](const Bin& b) -> const KernelVariant* {
     if (ball || self || b.tree || b.nvc > 16 || ncr_for(b.nvc) > 0) return nullptr;
     return find_variant(b.nvc, b.sb, 16, 0, 0);
   };
+  std::vector<char> flat(hp->bins.size(), 0);
+  bool any_flat = false;
+  for (size_t k = 0; k < hp->bins.size(); ++k) {
+    flat[k] = wide_budget(hp->bins[k]) && lies_on_many(*d, hp->bins[k].users, hp->q_off);
+    any_flat = any_flat || flat[k];
+  }
   // single launch: every bin must be one of the multi-bin kernel's families
-  auto find_multi = [&](Bin& b) {
-    const KernelVariant* kv = wide_budget(b);
+  auto find_multi = [&](Bin& b, const MultiSet& set) {
+    const KernelVariant* kv = &set == &multi_set1() ? wide_budget(b) : nullptr;
     const int ncr = kv ? kv->ncr : b.ncr;
-    for (int k = 0; k < kNumMultiFamilies; ++k)
-      if (kMultiFamilies[k].nvc == b.nvc && kMultiFamilies[k].sb == b.sb && kMultiFamilies[k].ncr == ncr)
-        b.multi_kind = k;
+    for (int k = 0; k < set.n; ++k)
+      if (set.families[k].nvc == b.nvc && set.families[k].sb == b.sb && set.families[k].ncr == ncr) b.multi_kind = k;
     return b.multi_kind >= 0;
   };
   if (hp->opts.single_launch) {
     if ((int)hp->bins.size() > kMaxMultiBins) return bad("single_launch supports at most 8 bins");
     if (ball || self) return bad("single_launch: the multi-bin kernel has no ball or self-collision families");
     for (Bin& b : hp->bins)
-      if (b.sb != 2 || !find_multi(b))
+      if (b.sb != 2 || !find_multi(b, multi_set1()))
         return bad("single_launch: bin (nv capacity " + std::to_string(b.nvc) + ", " + std::to_string(16 * b.sb) +
                    " bodies, " + std::to_string(b.ncr) + " contacts in registers) is not in the multi-bin kernel");
-    hp->multi = true;
+    hp->multi = &multi_set1();
   } else if (hp->opts.streams == 0 && !hp->opts.time_launches && !ball && !self && hp->bins.size() > 1 &&
              (int)hp->bins.size() <= kMaxMultiBins) {
     // Neither streams nor per-bin launch times asked for: several plane bins go
@@ -610,21 +614,22 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
     // 54.2 ms).  Every workgroup then has the largest family's registers, two
     // waves per SIMD: populations of small robots alone that need more of them
     // (three fit) keep their own launches.
+    const MultiSet& set = any_flat ? multi_set1() : multi_set0();
     long long waves = 0;
     bool covered = true, large = false, tree = false;
     for (Bin& b : hp->bins) {
       waves += ((long long)b.users.size() + kVarPerWave - 1) / kVarPerWave;
-      covered = find_multi(b) && covered;
+      covered = find_multi(b, set) && covered;
       large = large || b.nvc > 16;
       tree = tree || b.tree;
     }
-    hp->multi = covered && !tree && (large || waves <= 2 * kSimds);
+    if (covered && !tree && (large || waves <= 2 * kSimds)) hp->multi = &set;
   }
-  for (Bin& b : hp->bins) {
-    const KernelVariant* kv = wide_budget(b);
-    if (!kv || !(hp->multi || lies_on_many(*d, b.users, hp->q_off))) continue;
-    b.ncr = kv->ncr;
-    b.fn = kv->fn;
+  for (size_t k = 0; k < hp->bins.size(); ++k) {
+    const KernelVariant* kv = wide_budget(hp->bins[k]);
+    if (!kv || !(flat[k] || hp->multi == &multi_set1())) continue;
+    hp->bins[k].ncr = kv->ncr;
+    hp->bins[k].fn = kv->fn;
   }
   // streams: longest-first assignment of the bins to the least-loaded stream
   {

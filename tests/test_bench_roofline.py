@@ -33,7 +33,9 @@ def test_handle_tells_whether_the_bins_go_out_together(options, one):
 
 
 def test_the_bins_alone_keep_their_contacts_in_registers():
-    pop = W.random_trees(8200)                            # more than two waves a SIMD: apart, the default would be 8
+    flat = W.chain(10, ["+x"] * 10, [W.AXIS_Z] * 10, root_type=W.ROOT_FREE)
+    flat.half_ext[:] = W.BRICK_HALF                       # lies on every brick: its launch keeps 16 contacts, the snakes' too
+    pop = W.concat([W.snake(20), flat, W.quadrupeds(2)])
     h = S.Handle(pop)
     o = bench.per_bin_options({}, h.one_launch(), h.bins())
     assert h.one_launch() and S.Handle(pop, **o).bins() == h.bins()
@@ -79,8 +81,8 @@ def test_traffic_of_the_one_launch_is_recorded_per_layout(tmp_path, monkeypatch)
         with open(d / "c_counter_collection.csv", "w", newline="") as f:
             w = csv.writer(f)
             w.writerow(["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value"])
-            for i, (k, v) in enumerate([("simk::rollout_multi_kernel(simk::MultiArgs, simk::ModelParams)", 7), ("copy", 1 << 19),
-                                        ("simk::rollout_multi_kernel(simk::MultiArgs, simk::ModelParams)", 90),
+            for i, (k, v) in enumerate([("void simk::rollout_multi_kernel<0>(simk::MultiArgs, simk::ModelParams)", 7), ("copy", 1 << 19),
+                                        ("void simk::rollout_multi_kernel<0>(simk::MultiArgs, simk::ModelParams)", 90),
                                         ("void simk::rollout_kernel<28, 2, 8, false, false, false>(simk::BinArgs)", 3),
                                         ("void simk::rollout_kernel<28, 2, 8, false, false, false>(simk::BinArgs)", 40)]):
                 w.writerow([i, k, counter, v])

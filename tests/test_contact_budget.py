@@ -1,7 +1,7 @@
 """The contacts that a bin keeps in registers where no budget is asked for:
 families of up to 16 DoFs take 16 where most robots of the bin can lie on more
-than 8 corners (whatever their first orientation), or where all bins go out in
-one launch, else 8.  The budget never changes results."""
+than 8 corners (whatever their first orientation), or go out in one launch with
+such a bin, else 8.  The budget never changes results."""
 import numpy as np
 import pytest
 
@@ -61,11 +61,20 @@ def test_others_keep_8():
 def test_several_bins():
     small = W.concat([flat(40, 3), flat(30, 10)])
     assert _budgets(small) == _budgets(small, streams=2) == {(12, 16): 16, (16, 16): 16}
-    mixed = W.concat([W.snake(9000), flat(40, 10)])       # apart: three waves per SIMD
-    assert _budgets(mixed) == {(12, 16): 8, (16, 16): 16}
-    with_large = W.concat([W.snake(9000), W.quadrupeds(2)])   # one launch: two waves per SIMD anyway
-    assert _budgets(with_large) == {(12, 16): 16, (28, 32): 8}
-    assert _budgets(with_large, streams=2) == {(12, 16): 8, (28, 32): 8}
+    # in a launch of all bins one bin of flat robots brings 16 for every small bin, apart each has its own
+    mixed = W.concat([W.snake(40), flat(40, 10)])
+    assert _budgets(mixed) == {(12, 16): 16, (16, 16): 16}
+    assert _budgets(mixed, streams=2) == {(12, 16): 8, (16, 16): 16}
+    with_large = W.concat([W.snake(9000), W.quadrupeds(2)])
+    assert _budgets(with_large) == _budgets(with_large, streams=2) == {(12, 16): 8, (28, 32): 8}
+    with_flat = W.concat([flat(9000, 3), W.quadrupeds(2)])
+    assert _budgets(with_flat) == _budgets(with_flat, streams=2) == {(12, 16): 16, (28, 32): 8}
+    assert set(_budgets(W.random_trees(300)).values()) == {8}
+    for pop, o in ((with_large, {}), (with_flat, {}), (mixed, {}), (with_flat, dict(ncr_by_nvc={16: 8})),
+                   (W.random_trees(300), dict(ncr_by_nvc={16: 8, 20: 4}))):
+        h = S.Handle(pop, **o)
+        assert h.one_launch()
+        h.close()
 
 
 def test_a_budget_asked_for_stays():
@@ -83,6 +92,7 @@ def test_a_budget_asked_for_stays():
 @pytest.mark.gpu
 @pytest.mark.parametrize("make", [lambda: flat(3, 2), lambda: flat(5, 3), lambda: flat(4, 10),
                                   lambda: W.concat([flat(6, 3), flat(3, 10), W.boxes(2)]),
+                                  lambda: W.concat([W.snake(5), flat(3, 10), W.quadrupeds(3), flat(6, 2)]),
                                   lambda: W.concat([flat(6, 2), flat(5, 6), flat(3, 9), W.quadrupeds(3)])])
 def test_every_budget_gives_the_same_bits(make):
     pop = make()
