@@ -140,7 +140,7 @@ extern "C" int PH_CAT(simk_phase_read_, PHASE_TU)(unsigned long long* out, int c
 
 def units(csrc: str):
     """Kernel translation units that instantiate the per-bin rollout kernels
-    (the single-launch kernel's unit has no read routine and is not profiled)."""
+    (those of the single launch have no read routine and are not profiled)."""
     kd = os.path.join(csrc, "kernels")
     out = []
     for f in sorted(os.listdir(kd)):
@@ -149,6 +149,20 @@ def units(csrc: str):
                 if "rollout_inst.inc" in fh.read():
                     out.append(f[len("rollout_"):-4])
     return out
+
+
+def per_bin(pop, options: dict) -> dict:
+    """The options with a launch per bin: where all bins would go out in one
+    launch, whose kernel has no clocks, each on a stream of its own instead, with
+    the same contacts in registers."""
+    from . import sim as S
+    h = S.Handle(pop, **options)
+    one, bins = h.one_launch(), h.bins()
+    h.close()
+    if not one:
+        return options
+    return dict({k: v for k, v in options.items() if k != "single_launch"}, streams=len(bins),
+                ncr_by_nvc={b[0]: b[2] for b in bins})
 
 
 def run(dirname: str, options: dict, steps: int, n: int = 8192, say=print):
@@ -164,7 +178,7 @@ def run(dirname: str, options: dict, steps: int, n: int = 8192, say=print):
     lib = S.load()
     opts = {k: ({int(a): b for a, b in v.items()} if k == "ncr_by_nvc" else v) for k, v in options.items()}
     pop = W.random_trees(n)
-    sim = S.Simulator(pop, **opts)
+    sim = S.Simulator(pop, **per_bin(pop, opts))
     tus = units(os.path.join(os.path.abspath(dirname), "csrc"))
     buf = (C.c_ulonglong * 192)()
     for tu in tus:
