@@ -97,3 +97,10 @@ def test_traffic_of_the_one_launch_is_recorded_per_layout(tmp_path, monkeypatch)
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     assert bench.recorded_traffic("rollout_multi_kernel 28x2x8", 1000) == (90 * 2 + 90 * 2) * 1024
     assert bench.recorded_traffic("rollout_multi_kernel 24x2x8+28x2x8", 1000) is None
+
+
+def test_the_default_layout_of_the_benchmark_is_recorded():
+    h = S.Handle(W.random_trees(8192))
+    layout = "+".join(f"{b[0]}x{b[1] // 16}x{b[2]}" for b in sorted(h.bins()))
+    assert h.one_launch() and bench.recorded_traffic(f"rollout_multi_kernel {layout}", 1000) is not None
+    h.close()
