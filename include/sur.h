@@ -73,7 +73,8 @@ typedef struct sur_handle sur_handle;
 int sur_create(const sur_config* cfg, sur_handle** out);
 
 /* Device workspace: parameters, Adam moments, BF16 weight copies, gradients and
- * the activations of one training batch. */
+ * the activations of one training batch (room for 65536 rows, whatever
+ * max_batch). */
 int sur_workspace_bytes(const sur_handle* h, size_t* bytes);
 
 /* Attach the workspace and upload the initial parameters (host float
@@ -152,7 +153,7 @@ int sur_topk(sur_handle* h, int64_t n, const float* scores, int64_t k, int32_t* 
  * Every call on a GPU shares that GPU's copy: calls that overlap on one GPU
  * (concurrent streams, threads) race and must be serialised by the caller.
  * scores: device float [n]; out: device int32 [k]; stream as in sur_topk.
- * n > SUR_TOPK_NOALLOC_MAX, k outside [0, n] or NULL arrays give
+ * n > SUR_TOPK_NOALLOC_MAX (a limit of this call, not of its scratch), k outside [0, n] or NULL arrays give
  * SUR_E_INVALID without touching the device; a HIP error gives SUR_E_DEVICE.
  * err: optional host buffer of err_len bytes for the message (NULL allowed).
  */

@@ -71,7 +71,7 @@ constexpr uint16_t kNaN = 0x7FC0;
 // consecutive columns of one row and go to LDS as eight bytes.
 // 1 M rows: 472 us, 700 TFLOP/s; layer at a time, with the activations (1.5 KB a
 // row) through HBM, 1816 us.  10 007 rows: 10 us, 39 in four launches.  What bounds
-// it is the matrix cores (235 us at the rate products alone reach), the exact erf
+// it is the matrix cores (274 us at the 1200 TFLOP/s of a large product), the exact erf
 // of 768 GELUs a row (8 vector instructions each, up to 46 where values are large:
 // then 790 us) and the LDS reads, which the barriers of a layer keep apart.
 constexpr int kPredWaves = 8;

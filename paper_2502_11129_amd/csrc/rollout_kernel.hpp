@@ -878,8 +878,10 @@ __device__ __forceinline__ int row_min_i(int x) {
 // not sunk below the contact rows.  With the LDS areas at most 1/8 of a CU's
 // 160 KB, 8192 quadrupeds x 500 steps take 25.6 ms (39.3 with one wave per
 // SIMD), 32768 boxes with a ball x 1000 steps 48.9 ms with three waves (46.9 since; 66.1
-// with two, 113 with one).  12 contacts in registers, balls on the largest
-// robots and the tree-sparse inverse do not fit 256 and keep one wave.
+// with two, 113 with one).  28 DoFs with 12 contacts in registers or a ball do
+// not fit 256 and keep one wave; the tree-sparse inverse does (238), but its
+// matrices in LDS (24.5 KB a workgroup) leave room for six waves on a CU's four
+// SIMDs, so it is not held to 256.
 template <int NVC, int SB, int NCR, bool BALL, bool SELF, bool TREE>
 struct WavesPerSimd {
   static constexpr int value = TREE || NCR > 8 && NVC > 16 || BALL && NVC > 24 ? 1

@@ -608,12 +608,15 @@ int sim_create(const sim_model_desc* d, const sim_options* opts, sim_handle** ou
     // out in one launch.  On their own streams they depend on the process's
     // four hardware queues: more bins than queues, or other handles' streams,
     // put two bins in one queue, which then run after each other.  4096 / 8192 /
-    // 32768 random trees x 1000 steps take 33.5 / 36.7 / 109 ms in one launch and
-    // 57.3 / 59.7 / 111 ms on six streams; four merged bins on four streams match
-    // it (34.0 / 36.2 / 110 ms) until three handles take turns (36.7 against
-    // 54.2 ms).  Every workgroup then has the largest family's registers, two
-    // waves per SIMD: populations of small robots alone that need more of them
-    // (three fit) keep their own launches.
+    // 32768 random trees x 1000 steps take 33.5 / 36.7 / 109 ms in one launch (8192
+    // 35.7 to 40.5 from run to run) and 57.3 / 59.7 / 111 ms on six streams; four
+    // merged bins on four streams match it (34.0 / 36.2 / 110 ms) until three
+    // handles take turns (36.7 against 54.2 ms).  Every workgroup then has the
+    // largest family's registers, two waves per SIMD: populations of small robots
+    // alone that need more of them (three fit) keep their own launches.  With a few
+    // large robots among them the large ones' latency is most of the time: beside 8
+    // quadrupeds, 500 steps, 32768 boxes take 20.1 ms in one launch and 21.1 on two
+    // streams, 32768 snakes 37.8 and 31.3.
     const MultiSet& set = any_flat ? multi_set1() : multi_set0();
     long long waves = 0;
     bool covered = true, large = false, tree = false;

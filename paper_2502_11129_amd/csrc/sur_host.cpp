@@ -7,7 +7,6 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <algorithm>
 #include <vector>
 
 #include "sur_launch.h"
@@ -16,7 +15,9 @@ using namespace surk;
 
 namespace {
 
-constexpr int64_t kWorkspaceRows = 65536;  // rows the workspace holds at least (sur_workspace_bytes as ever)
+// Rows of a training batch that every workspace holds: the largest max_batch, so
+// that sur_workspace_bytes is the same for all of them.
+constexpr int64_t kWorkspaceRows = 65536;
 
 struct Work {
   float *p, *m, *v, *g;
@@ -73,7 +74,7 @@ static int ready(sur_handle* h) {
 }
 
 // Workspace layout: 256-byte aligned regions in a fixed order.
-static size_t layout(const sur_handle* h, char* base, Work* w) {
+static size_t layout(char* base, Work* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
     off = (off + 255) & ~size_t(255);
@@ -81,7 +82,7 @@ static size_t layout(const sur_handle* h, char* base, Work* w) {
     off += bytes;
     return p;
   };
-  const int64_t R = std::max<int64_t>(h->cfg.max_batch, kWorkspaceRows);
+  const int64_t R = kWorkspaceRows;
   Work x{};
   x.p = (float*)take(sizeof(float) * kNParams);
   x.m = (float*)take(sizeof(float) * kNParams);
@@ -119,14 +120,14 @@ int sur_create(const sur_config* cfg, sur_handle** out) {
   if (!out) return fail(nullptr, SUR_E_INVALID, "out is NULL");
   *out = nullptr;
   if (!cfg) return fail(nullptr, SUR_E_INVALID, "cfg is NULL");
-  if (cfg->max_batch < 1 || cfg->max_batch > 65536)
+  if (cfg->max_batch < 1 || cfg->max_batch > kWorkspaceRows)
     return fail(nullptr, SUR_E_INVALID, "max_batch must be in [1, 65536]");
   if (!(cfg->lr > 0.0) || !(cfg->beta1 >= 0.0 && cfg->beta1 < 1.0) || !(cfg->beta2 >= 0.0 && cfg->beta2 < 1.0) ||
       !(cfg->eps > 0.0))
     return fail(nullptr, SUR_E_INVALID, "Adam settings out of range (lr > 0, 0 <= beta < 1, eps > 0)");
   sur_handle* h = new sur_handle();
   h->cfg = *cfg;
-  h->bytes = layout(h, nullptr, nullptr);
+  h->bytes = layout(nullptr, nullptr);
   *out = h;
   return SUR_OK;
 }
@@ -144,7 +145,7 @@ int sur_bind(sur_handle* h, void* ws, size_t bytes, const float* init, void* str
   if (!init) return fail(h, SUR_E_INVALID, "init_params is NULL");
   hipStream_t s = (hipStream_t)stream;
   h->base = (char*)ws;
-  layout(h, h->base, &h->w);
+  layout(h->base, &h->w);
   const size_t pb = sizeof(float) * kNParams;
   SUR_HIP(h, hipMemcpyAsync(h->w.p, init, pb, hipMemcpyHostToDevice, s), "upload parameters");
   std::vector<float> zero(kNParams, 0.f);
@@ -334,7 +335,7 @@ int sur_topk_noalloc(int64_t n, const float* scores, int64_t k, int32_t* out, vo
   static_assert(SUR_TOPK_NOALLOC_MAX == kTopkStaticMax, "header and scratch size agree");
   if (n < 0 || k < 0 || k > n) return fail_msg(SUR_E_INVALID, "need 0 <= k <= n");
   if (n > SUR_TOPK_NOALLOC_MAX)
-    return fail_msg(SUR_E_INVALID, "n exceeds SUR_TOPK_NOALLOC_MAX (16777216 scores), the size of the static scratch");
+    return fail_msg(SUR_E_INVALID, "n exceeds SUR_TOPK_NOALLOC_MAX (16777216 scores)");
   if (k == 0) return SUR_OK;
   if (!scores || !out) return fail_msg(SUR_E_INVALID, "NULL array");
   const hipError_t e = topk_noalloc(n, scores, k, out, (hipStream_t)stream);

@@ -83,7 +83,8 @@ struct TopkScratch {
 };
 hipError_t topk(int64_t n, const float* scores, int64_t k, int32_t* out, const TopkScratch& ws, hipStream_t s);
 // The same selection with its scratch in a static device array of the library
-// (no allocation, no workspace argument); n <= kTopkStaticMax.
+// (no allocation, no workspace argument); n <= kTopkStaticMax, the limit of the
+// C call (the scratch is enough for any n).
 constexpr int64_t kTopkStaticMax = int64_t(1) << 24;
 hipError_t topk_noalloc(int64_t n, const float* scores, int64_t k, int32_t* out, hipStream_t s);
 
